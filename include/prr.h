@@ -317,8 +317,9 @@ typedef struct {
 } prr_step_params;
 
 #define PRR_SCHED_SERIAL 0     /* per layer: select, then attend every page of A (one stream) */
-#define PRR_SCHED_TWO_STREAM 1 /* per layer: select on `stream` while speculating over P on `spec_stream`,
-                                  repair on `stream`, EMA update + next prediction on `spec_stream` */
+#define PRR_SCHED_TWO_STREAM 1 /* per layer: select while speculating over P, then repair while updating the EMA
+                                  and predicting.  Each pair is one launch on `stream`; the step starts after
+                                  earlier work on both streams, and later work on either starts after it */
 #define PRR_SCHED_PREFILL 2    /* per layer: select, then initialise the EMA state and predict P (step 0) */
 /* The same three steps, each layer as ONE launch on `stream` whose workgroups take the
  * roles of the separate kernels (score, select, predict, speculate, attend missed pages,
@@ -334,9 +335,9 @@ typedef struct {
 
 /* One decode step over n_layers layers in order (layer l+1 starts after layer l's output is
  * written on `stream`): the select / speculate / repair / predict steps of Fig. 1 and
- * Section 4 launched from native code with the fork/join of two streams.
+ * Section 4, launched from native code.
  *   events      host [3 * n_layers + 1] hipEvent_t created by the caller (timing may be
- *               disabled) for the fork/join of PRR_SCHED_TWO_STREAM, else ignored; NULL
+ *               disabled) that order the two streams in PRR_SCHED_TWO_STREAM, else ignored; NULL
  *               with PRR_SCHED_TWO_STREAM orders the two streams with stream memory writes
  *               and waits instead (hipStreamWriteValue64 / hipStreamWaitValue64 on four
  *               64-bit words that the library allocates once per device and keeps until the
@@ -347,7 +348,7 @@ typedef struct {
  *               they may.  PRR_ERR_UNSUPPORTED when the device has no stream memory waits.
  *   parity      0 or 1: which predicted buffer holds P^t
  * When the call returns every launch is enqueued; all work of the step is ordered
- * before any later work on `stream` (the speculation stream is joined back).  The
+ * before any later work on `stream` and on `spec_stream`.  The
  * arguments of every layer are validated as by the individual calls; on an error in
  * layer l, layers before l have been enqueued. */
 prr_status prr_decode_step(const prr_dims* dims, const prr_step_params* params, const prr_layer_io* layers,

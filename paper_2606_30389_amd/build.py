@@ -12,8 +12,8 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["csrc/prr_kernels.hip", "csrc/prr_fused_bf16.hip", "csrc/prr_fused_f16.hip", "csrc/prr_fused_p64.hip",
-           "csrc/prr_api.cpp", "csrc/prr_calibrate.cpp", "csrc/prr_budget.cpp",
+SOURCES = ["csrc/prr_kernels.hip", "csrc/prr_sep_bf16.hip", "csrc/prr_sep_f16.hip", "csrc/prr_fused_bf16.hip",
+           "csrc/prr_fused_f16.hip", "csrc/prr_fused_p64.hip", "csrc/prr_api.cpp", "csrc/prr_calibrate.cpp", "csrc/prr_budget.cpp",
            "csrc/prr_noalloc.hip"]
 OUT = os.path.join(HERE, "libprr.so")
 OBJ_DIR = os.path.join(ROOT, "_build", "obj")

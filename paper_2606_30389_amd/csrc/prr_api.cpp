@@ -78,10 +78,12 @@ prr_status check_ptr(const void* p, const char* name, size_t align) {
     if (_s != PRR_OK) return _s;   \
   } while (0)
 
+constexpr int kCounterStride = 64;  // words between the arrival counters of two KV heads
+
 struct WsLayout {
-  size_t flags, sel_cnt, rep_cnt, rep_o, rep_ml, f_score, f_thr, f_mcnt, f_mlist, f_part, f_parto, f_candk,
-      f_candp, f_pkey, f_win, f_lcnt, f_pbits, total;
-  int nchunks, nwork_max, nparts;
+  size_t flags, sel_cnt, sel_pcnt, sel_gmax, ema_cnt, rep_o, rep_ml, f_score, f_thr, f_mcnt, f_mlist, f_part, f_parto, f_candk,
+      f_candp, f_pkey, f_win, f_lcnt, f_pbits, ema_gmax, ema_keys, total;
+  int nchunks, nwork_max, nparts, gmax_stride;
 };
 
 bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
@@ -94,8 +96,14 @@ bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
   off += 256;
   L.sel_cnt = off;
   off = align_up(off + (size_t)hkv * 4, 256);
-  L.rep_cnt = off;
-  off = align_up(off + (size_t)2 * hkv * 4, 256);
+  // the same counters on lines of their own: hundreds of workgroups of many KV heads add to them
+  L.sel_pcnt = off;
+  off += (size_t)hkv * kCounterStride * 4;
+  L.gmax_stride = div_up(d->max_pages, 4);  // (groups of at least four pages)
+  L.sel_gmax = off;
+  off = align_up(off + (size_t)hkv * L.gmax_stride * 4, 256);
+  L.ema_cnt = off;
+  off += (size_t)hkv * kCounterStride * 4;
   L.rep_o = off;
   off = align_up(off + (size_t)hkv * L.nwork_max * g * 128 * 4, 256);
   L.rep_ml = off;
@@ -128,6 +136,11 @@ bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
   off = align_up(off + (size_t)hkv * 8 * 256, 256);
   L.f_pbits = off;
   off = align_up(off + 2 * (size_t)hkv * ((d->max_pages + 31) / 32) * 4, 256);
+  // the two-stream step's EMA update: keys and their group maxima
+  L.ema_gmax = off;
+  off = align_up(off + (size_t)hkv * L.gmax_stride * 4, 256);
+  L.ema_keys = off;
+  off = align_up(off + (size_t)hkv * d->max_pages * 4, 256);
   L.total = off;
   return true;
 }
@@ -183,7 +196,7 @@ void budget(int k_select, int n_forced, int forced_in_budget, int num_pages, int
 }
 
 // Events and stream-memory words of prr_stream_chain (words 0, 1) and of the two-stream
-// step without events (words 2-5: fork, selection, speculation, join), made once per device
+// step without events (words 2-5: both ways at its start and at its end), made once per device
 // and kept until the process ends (a stream may still wait on them when a call returns).
 // Every value written is larger than the one before, so each word only grows.
 constexpr int kChainMaxHops = 256;
@@ -437,25 +450,41 @@ prr_status prr_build_page_meta(const prr_dims* dims, const void* k_cache, const 
   return hip_status(prr::launch_meta(a, stream), "build_page_meta launch");
 }
 
+static prr_status score_args(const prr_dims* dims, const void* q, const void* meta, int32_t num_pages, int32_t k_select,
+                             const int32_t* forced, int32_t n_forced, int32_t forced_in_budget, float* scores,
+                             int32_t* selected, int32_t* selected_count, int32_t cap, void* workspace, size_t ws_bytes,
+                             prr::ScoreLaunch& a) {
+  PRR_TRY(prr::prepare_score(dims, q, meta, num_pages, k_select, forced, n_forced, forced_in_budget, scores, selected,
+                             selected_count, cap, a));
+  PRR_TRY(check_ptr(workspace, "workspace", 256));
+  WsLayout L;
+  if (!ws_layout(dims, cap, 1, L) || ws_bytes < L.sel_pcnt)
+    return fail(PRR_ERR_WORKSPACE, "workspace of %zu bytes too small", ws_bytes);
+  char* ws = static_cast<char*>(workspace);
+  const bool room = ws_bytes >= L.ema_cnt;
+  a.counters = reinterpret_cast<uint32_t*>(ws + (room ? L.sel_pcnt : L.sel_cnt));
+  a.cnt_stride = room ? kCounterStride : 1;
+  // (these regions lie ahead of every one whose place depends on the chunk; a workspace that
+  // holds the counters alone does, at the cost of a slower select)
+  a.gmax = room ? reinterpret_cast<uint32_t*>(ws + L.sel_gmax) : nullptr;
+  a.gmax_stride = L.gmax_stride;
+  return ok();
+}
+
 prr_status prr_score_topk(const prr_dims* dims, const void* q, const void* meta, int32_t num_pages, int32_t k_select,
                           const int32_t* forced, int32_t n_forced, int32_t forced_in_budget, float* scores,
                           int32_t* selected, int32_t* selected_count, int32_t cap, void* workspace, size_t ws_bytes,
                           hipStream_t stream) {
   prr::ScoreLaunch a;
-  PRR_TRY(prr::prepare_score(dims, q, meta, num_pages, k_select, forced, n_forced, forced_in_budget, scores, selected,
-                             selected_count, cap, a));
-  PRR_TRY(check_ptr(workspace, "workspace", 256));
-  WsLayout L;
-  if (!ws_layout(dims, cap, 1, L) || ws_bytes < L.rep_cnt)
-    return fail(PRR_ERR_WORKSPACE, "workspace of %zu bytes too small", ws_bytes);
-  a.counters = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + L.sel_cnt);
+  PRR_TRY(score_args(dims, q, meta, num_pages, k_select, forced, n_forced, forced_in_budget, scores, selected,
+                     selected_count, cap, workspace, ws_bytes, a));
   return hip_status(prr::launch_score_topk(a, stream), "score_topk launch");
 }
 
-prr_status prr_predict(const prr_dims* dims, float* ema_level, float* ema_trend, uint32_t* ema_init_bits,
-                       const float* scores, int32_t num_pages, float alpha, float beta, float gamma, int32_t p_select,
-                       const int32_t* forced, int32_t n_forced, int32_t forced_in_budget, int32_t* predicted,
-                       int32_t* predicted_count, int32_t cap, hipStream_t stream) {
+static prr_status predict_args(const prr_dims* dims, float* ema_level, float* ema_trend, uint32_t* ema_init_bits,
+                               const float* scores, int32_t num_pages, float alpha, float beta, float gamma,
+                               int32_t p_select, const int32_t* forced, int32_t n_forced, int32_t forced_in_budget,
+                               int32_t* predicted, int32_t* predicted_count, int32_t cap, prr::PredictLaunch& a) {
   PRR_TRY(check_dims(dims));
   PRR_TRY(check_ptr(ema_level, "ema_level", 4));
   PRR_TRY(check_ptr(ema_trend, "ema_trend", 4));
@@ -473,7 +502,6 @@ prr_status prr_predict(const prr_dims* dims, float* ema_level, float* ema_trend,
   int total, kextra;
   budget(p_select, n_forced, forced_in_budget, num_pages, total, kextra);
   if (total > cap) return fail(PRR_ERR_INVALID_ARG, "|P| = %d exceeds cap %d", total, cap);
-  prr::PredictLaunch a;
   memset(&a, 0, sizeof(a));
   a.level = ema_level;
   a.trend = ema_trend;
@@ -491,13 +519,33 @@ prr_status prr_predict(const prr_dims* dims, float* ema_level, float* ema_trend,
   a.cap = cap;
   a.n_forced = n_forced;
   for (int i = 0; i < n_forced; ++i) a.forced[i] = forced[i];
+  return ok();
+}
+
+prr_status prr_predict(const prr_dims* dims, float* ema_level, float* ema_trend, uint32_t* ema_init_bits,
+                       const float* scores, int32_t num_pages, float alpha, float beta, float gamma, int32_t p_select,
+                       const int32_t* forced, int32_t n_forced, int32_t forced_in_budget, int32_t* predicted,
+                       int32_t* predicted_count, int32_t cap, hipStream_t stream) {
+  prr::PredictLaunch a;
+  PRR_TRY(predict_args(dims, ema_level, ema_trend, ema_init_bits, scores, num_pages, alpha, beta, gamma, p_select,
+                       forced, n_forced, forced_in_budget, predicted, predicted_count, cap, a));
   return hip_status(prr::launch_predict(a, stream), "predict launch");
 }
 
-prr_status prr_spec_attn(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
-                         const int32_t* page_table, int32_t num_tokens, const int32_t* pages,
-                         const int32_t* page_count, int32_t cap, int32_t chunk_pages, float* part_o, float* part_m,
-                         float* part_l, float* page_m, hipStream_t stream) {
+// The scratch of the EMA update spread over many workgroups (the workspace holds L.total).
+static void predict_scratch(void* workspace, const WsLayout& L, prr::PredictLaunch& a) {
+  char* ws = static_cast<char*>(workspace);
+  a.counters = reinterpret_cast<uint32_t*>(ws + L.ema_cnt);
+  a.cnt_stride = kCounterStride;
+  a.keys = reinterpret_cast<uint32_t*>(ws + L.ema_keys);
+  a.gmax = reinterpret_cast<uint32_t*>(ws + L.ema_gmax);
+  a.gmax_stride = L.gmax_stride;
+}
+
+static prr_status spec_args(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
+                            const int32_t* page_table, int32_t num_tokens, const int32_t* pages,
+                            const int32_t* page_count, int32_t cap, int32_t chunk_pages, float* part_o, float* part_m,
+                            float* part_l, float* page_m, prr::SpecLaunch& a) {
   PRR_TRY(check_dims(dims));
   PRR_TRY(check_ptr(q, "q", 16));
   PRR_TRY(check_ptr(k_cache, "k_cache", 16));
@@ -514,7 +562,6 @@ prr_status prr_spec_attn(const prr_dims* dims, const void* q, const void* k_cach
   if (cap < 1 || cap > PRR_MAX_CAP) return fail(PRR_ERR_INVALID_ARG, "cap %d outside [1, %d]", cap, PRR_MAX_CAP);
   if (!chunk_ok(dims, chunk_pages))
     return fail(PRR_ERR_INVALID_ARG, "chunk_pages %d outside [1, 256 / page_size]", chunk_pages);
-  prr::SpecLaunch a;
   memset(&a, 0, sizeof(a));
   a.q = q;
   a.k_cache = k_cache;
@@ -536,16 +583,26 @@ prr_status prr_spec_attn(const prr_dims* dims, const void* q, const void* k_cach
   a.chunk = chunk_pages;
   a.nchunks = div_up(cap, chunk_pages);
   a.bf16 = dims->dtype == PRR_BF16;
+  return ok();
+}
+
+prr_status prr_spec_attn(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
+                         const int32_t* page_table, int32_t num_tokens, const int32_t* pages,
+                         const int32_t* page_count, int32_t cap, int32_t chunk_pages, float* part_o, float* part_m,
+                         float* part_l, float* page_m, hipStream_t stream) {
+  prr::SpecLaunch a;
+  PRR_TRY(spec_args(dims, q, k_cache, v_cache, page_table, num_tokens, pages, page_count, cap, chunk_pages, part_o,
+                    part_m, part_l, page_m, a));
   return hip_status(prr::launch_spec_attn(a, stream), "spec_attn launch");
 }
 
-prr_status prr_repair(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
+static prr_status repair_args(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
                       const int32_t* page_table, int32_t num_tokens, int32_t num_pages, const int32_t* selected,
                       const int32_t* selected_count, const int32_t* predicted, const int32_t* predicted_count,
                       int32_t cap, int32_t chunk_pages, const float* part_o, const float* part_m, const float* part_l,
                       const float* page_m, int32_t mode, float* out_o32, void* out_o, float* out_m, float* out_l,
                       int32_t* missed_count, int32_t* wasted_count, void* workspace, size_t ws_bytes,
-                      hipStream_t stream) {
+                      WsLayout& L, prr::RepairLaunch& a) {
   PRR_TRY(check_dims(dims));
   PRR_TRY(check_ptr(q, "q", 16));
   PRR_TRY(check_ptr(k_cache, "k_cache", 16));
@@ -578,12 +635,10 @@ prr_status prr_repair(const prr_dims* dims, const void* q, const void* k_cache, 
   if (!chunk_ok(dims, chunk_pages))
     return fail(PRR_ERR_INVALID_ARG, "chunk_pages %d outside [1, 256 / page_size]", chunk_pages);
   PRR_TRY(check_ptr(workspace, "workspace", 256));
-  WsLayout L;
   if (!ws_layout(dims, cap, chunk_pages, L) || ws_bytes < L.total)
     return fail(PRR_ERR_WORKSPACE, "workspace of %zu bytes too small (need %zu)", ws_bytes,
                 ws_layout(dims, cap, chunk_pages, L) ? L.total : (size_t)0);
   const int g = dims->num_q_heads / dims->num_kv_heads;
-  prr::RepairLaunch a;
   memset(&a, 0, sizeof(a));
   a.q = q;
   a.k_cache = k_cache;
@@ -605,8 +660,7 @@ prr_status prr_repair(const prr_dims* dims, const void* q, const void* k_cache, 
   a.wasted_count = wasted_count;
   char* ws = static_cast<char*>(workspace);
   a.ws_o = reinterpret_cast<float*>(ws + L.rep_o);
-  a.ws_ml = reinterpret_cast<float*>(ws + L.rep_ml);
-  a.ws_cnt = reinterpret_cast<uint32_t*>(ws + L.rep_cnt);
+  a.ws_ml = reinterpret_cast<uint64_t*>(ws + L.rep_ml);
   a.flags = reinterpret_cast<uint32_t*>(ws + L.flags);
   a.num_kv_heads = dims->num_kv_heads;
   a.group = g;
@@ -618,9 +672,23 @@ prr_status prr_repair(const prr_dims* dims, const void* q, const void* k_cache, 
   a.chunk = chunk_pages;
   a.nchunks = L.nchunks;
   a.nwork = (predicted && mode == PRR_EXACT_SELECTED) ? 2 * L.nchunks : L.nchunks;
-  a.nmerge_per_kv = div_up(g, 2);
   a.mode = mode;
   a.bf16 = dims->dtype == PRR_BF16;
+  return ok();
+}
+
+prr_status prr_repair(const prr_dims* dims, const void* q, const void* k_cache, const void* v_cache,
+                      const int32_t* page_table, int32_t num_tokens, int32_t num_pages, const int32_t* selected,
+                      const int32_t* selected_count, const int32_t* predicted, const int32_t* predicted_count,
+                      int32_t cap, int32_t chunk_pages, const float* part_o, const float* part_m, const float* part_l,
+                      const float* page_m, int32_t mode, float* out_o32, void* out_o, float* out_m, float* out_l,
+                      int32_t* missed_count, int32_t* wasted_count, void* workspace, size_t ws_bytes,
+                      hipStream_t stream) {
+  WsLayout L;
+  prr::RepairLaunch a;
+  PRR_TRY(repair_args(dims, q, k_cache, v_cache, page_table, num_tokens, num_pages, selected, selected_count, predicted,
+                      predicted_count, cap, chunk_pages, part_o, part_m, part_l, page_m, mode, out_o32, out_o, out_m,
+                      out_l, missed_count, wasted_count, workspace, ws_bytes, L, a));
   return hip_status(prr::launch_repair(a, stream), "repair launch");
 }
 
@@ -830,6 +898,60 @@ static prr_status fused_layer(const prr_dims* dims, const prr_step_params* sp, c
   return hip_status(prr::launch_fused(a, dims->dtype == PRR_BF16, dims->page_size, stream), "fused step launch");
 }
 
+// The two-stream step (Fig. 1).  What the paper overlaps on two streams needs nothing from each
+// other, so each layer is two launches on `stream`: select beside speculate, then repair beside
+// the EMA update and prediction.  A dependency between two streams costs 5-12 us here, three of
+// them per layer 20 us and more of a 53 us layer step (128K tokens, 128-token pages, 8 KV heads);
+// what remains of them is one pair at the start, which orders the step after earlier work on
+// both streams, and one wait of `spec_stream` at the end, off the step's path.
+static prr_status two_stream_step(const prr_dims* dims, const prr_step_params* sp, const prr_layer_io* layers,
+                                  int32_t n_layers, int32_t parity, hipStream_t stream, hipStream_t spec_stream,
+                                  hipEvent_t* events) {
+  // without events the library's stream-memory words order the streams
+  ChainState* mem = nullptr;
+  std::unique_lock<std::mutex> mem_lock(g_chain_mu, std::defer_lock);
+  if (!events) {
+    PRR_TRY(chain_state(mem));
+    mem_lock.lock();
+    PRR_TRY(stream_words(*mem, stream));
+  }
+  const auto event = [&](int i) { return mem ? nullptr : events[i]; };
+  PRR_TRY(stream_dep(stream, spec_stream, event(0), mem, 2));
+  PRR_TRY(stream_dep(spec_stream, stream, event(1), mem, 3));
+  for (int l = 0; l < n_layers; ++l) {
+    const prr_layer_io& y = layers[l];
+    const float* th = y.theta ? y.theta : &sp->alpha;  // (alpha, beta, gamma are consecutive)
+    PRR_TRY(check_theta(th));
+    prr::ScoreLaunch sc;
+    prr::SpecLaunch at;
+    prr::RepairLaunch re;
+    prr::PredictLaunch pr;
+    WsLayout L;
+    PRR_TRY(score_args(dims, y.q, y.meta, sp->num_pages, sp->k_select, sp->forced, sp->n_forced, sp->forced_in_budget,
+                       y.scores, y.selected, y.selected_count, sp->cap, y.workspace, y.ws_bytes, sc));
+    PRR_TRY(spec_args(dims, y.q, y.k_cache, y.v_cache, y.page_table, sp->num_tokens, y.predicted[parity],
+                      y.predicted_count[parity], sp->cap, sp->chunk_pages, y.part_o, y.part_m, y.part_l, y.page_m, at));
+    PRR_TRY(repair_args(dims, y.q, y.k_cache, y.v_cache, y.page_table, sp->num_tokens, sp->num_pages, y.selected,
+                        y.selected_count, y.predicted[parity], y.predicted_count[parity], sp->cap, sp->chunk_pages,
+                        y.part_o, y.part_m, y.part_l, y.page_m, sp->mode, y.out_o32, y.out_o, y.out_m, y.out_l,
+                        y.missed_count, y.wasted_count, y.workspace, y.ws_bytes, L, re));
+    PRR_TRY(predict_args(dims, y.ema_level, y.ema_trend, y.ema_init_bits, y.scores, sp->num_pages, th[0], th[1], th[2],
+                         sp->p_select, sp->forced, sp->n_forced, sp->forced_in_budget, y.predicted[1 - parity],
+                         y.predicted_count[1 - parity], sp->cap, pr));
+    predict_scratch(y.workspace, L, pr);
+    PRR_TRY(hip_status(prr::launch_select_spec(sc, at, stream), "select + speculate launch"));
+    PRR_TRY(hip_status(prr::launch_repair_predict(re, pr, stream), "repair + predict launch"));
+  }
+  // later work on the speculation stream comes after the step, as it would had the predictions
+  // been made there
+  PRR_TRY(stream_dep(stream, spec_stream, event(2), mem, 4));
+  // (a captured stream has to be joined back; outside a capture nothing is left to wait for)
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
+  if (capturing == hipStreamCaptureStatusActive) PRR_TRY(stream_dep(spec_stream, stream, event(3), mem, 5));
+  return ok();
+}
+
 prr_status prr_decode_step(const prr_dims* dims, const prr_step_params* sp, const prr_layer_io* layers,
                            int32_t n_layers, int32_t parity, int32_t schedule, hipStream_t stream,
                            hipStream_t spec_stream, hipEvent_t* events) {
@@ -846,63 +968,32 @@ prr_status prr_decode_step(const prr_dims* dims, const prr_step_params* sp, cons
     for (int l = 0; l < n_layers; ++l) PRR_TRY(fused_layer(dims, sp, layers[l], parity, schedule, stream, l));
     return ok();
   }
-  // PRR_SCHED_TWO_STREAM without events: the library's stream-memory words order the streams
-  ChainState* mem = nullptr;
-  std::unique_lock<std::mutex> mem_lock(g_chain_mu, std::defer_lock);
-  if (schedule == PRR_SCHED_TWO_STREAM && !events) {
-    PRR_TRY(chain_state(mem));
-    mem_lock.lock();
-    PRR_TRY(stream_words(*mem, stream));
-  }
+  if (schedule == PRR_SCHED_TWO_STREAM)
+    return two_stream_step(dims, sp, layers, n_layers, parity, stream, spec_stream, events);
   const int nxt = 1 - parity;
   for (int l = 0; l < n_layers; ++l) {
     const prr_layer_io& y = layers[l];
     const float* th = y.theta ? y.theta : &sp->alpha;  // (alpha, beta, gamma are consecutive)
     if (schedule != PRR_SCHED_SERIAL) PRR_TRY(check_theta(th));
+    PRR_TRY(prr_score_topk(dims, y.q, y.meta, sp->num_pages, sp->k_select, sp->forced, sp->n_forced,
+                           sp->forced_in_budget, y.scores, y.selected, y.selected_count, sp->cap, y.workspace,
+                           y.ws_bytes, stream));
     if (schedule == PRR_SCHED_SERIAL) {
-      PRR_TRY(prr_score_topk(dims, y.q, y.meta, sp->num_pages, sp->k_select, sp->forced, sp->n_forced,
-                             sp->forced_in_budget, y.scores, y.selected, y.selected_count, sp->cap, y.workspace,
-                             y.ws_bytes, stream));
       PRR_TRY(prr_repair(dims, y.q, y.k_cache, y.v_cache, y.page_table, sp->num_tokens, sp->num_pages, y.selected,
                          y.selected_count, nullptr, nullptr, sp->cap, sp->chunk_pages, nullptr, nullptr, nullptr,
                          nullptr, sp->mode, y.out_o32, y.out_o, y.out_m, y.out_l, y.missed_count, y.wasted_count,
                          y.workspace, y.ws_bytes, stream));
-    } else if (schedule == PRR_SCHED_PREFILL) {
-      PRR_TRY(prr_score_topk(dims, y.q, y.meta, sp->num_pages, sp->k_select, sp->forced, sp->n_forced,
-                             sp->forced_in_budget, y.scores, y.selected, y.selected_count, sp->cap, y.workspace,
-                             y.ws_bytes, stream));
-      PRR_TRY(prr_predict(dims, y.ema_level, y.ema_trend, y.ema_init_bits, y.scores, sp->num_pages, th[0], th[1],
-                          th[2], sp->p_select, sp->forced, sp->n_forced, sp->forced_in_budget,
-                          y.predicted[nxt], y.predicted_count[nxt], sp->cap, stream));
     } else {
-      hipEvent_t fork = mem ? nullptr : events[3 * l], sel = mem ? nullptr : events[3 * l + 1],
-                 spec = mem ? nullptr : events[3 * l + 2];
-      PRR_TRY(stream_dep(stream, spec_stream, fork, mem, 2));
-      PRR_TRY(prr_score_topk(dims, y.q, y.meta, sp->num_pages, sp->k_select, sp->forced, sp->n_forced,
-                             sp->forced_in_budget, y.scores, y.selected, y.selected_count, sp->cap, y.workspace,
-                             y.ws_bytes, stream));
-      // (the selection's point on `stream`, waited for by the prediction below)
-      const uint64_t sel_value = mem ? ++mem->value : 0;
-      if (mem) PRR_TRY(hip_status(hipStreamWriteValue64(stream, mem->word[3], sel_value, 0), "stream write"));
-      else PRR_TRY(hip_status(hipEventRecord(sel, stream), "event record"));
-      PRR_TRY(prr_spec_attn(dims, y.q, y.k_cache, y.v_cache, y.page_table, sp->num_tokens, y.predicted[parity],
-                            y.predicted_count[parity], sp->cap, sp->chunk_pages, y.part_o, y.part_m, y.part_l,
-                            y.page_m, spec_stream));
-      PRR_TRY(stream_dep(spec_stream, stream, spec, mem, 4));
-      PRR_TRY(prr_repair(dims, y.q, y.k_cache, y.v_cache, y.page_table, sp->num_tokens, sp->num_pages, y.selected,
-                         y.selected_count, y.predicted[parity], y.predicted_count[parity], sp->cap, sp->chunk_pages,
-                         y.part_o, y.part_m, y.part_l, y.page_m, sp->mode, y.out_o32, y.out_o, y.out_m, y.out_l,
-                         y.missed_count, y.wasted_count, y.workspace, y.ws_bytes, stream));
-      if (mem)
-        PRR_TRY(hip_status(hipStreamWaitValue64(spec_stream, mem->word[3], sel_value, hipStreamWaitValueGte, ~0ull),
-                           "stream wait"));
-      else PRR_TRY(hip_status(hipStreamWaitEvent(spec_stream, sel, 0), "stream wait"));
-      PRR_TRY(prr_predict(dims, y.ema_level, y.ema_trend, y.ema_init_bits, y.scores, sp->num_pages, th[0], th[1],
-                          th[2], sp->p_select, sp->forced, sp->n_forced, sp->forced_in_budget,
-                          y.predicted[nxt], y.predicted_count[nxt], sp->cap, spec_stream));
+      prr::PredictLaunch a;
+      PRR_TRY(predict_args(dims, y.ema_level, y.ema_trend, y.ema_init_bits, y.scores, sp->num_pages, th[0], th[1],
+                           th[2], sp->p_select, sp->forced, sp->n_forced, sp->forced_in_budget, y.predicted[nxt],
+                           y.predicted_count[nxt], sp->cap, a));
+      WsLayout L;
+      const bool room = ws_layout(dims, sp->cap, sp->chunk_pages, L) && y.ws_bytes >= L.total;
+      if (room) predict_scratch(y.workspace, L, a);
+      PRR_TRY(hip_status(room ? prr::launch_ema_topk(a, stream) : prr::launch_predict(a, stream), "predict launch"));
     }
   }
-  if (schedule == PRR_SCHED_TWO_STREAM) PRR_TRY(stream_dep(spec_stream, stream, mem ? nullptr : events[3 * n_layers], mem, 5));
   return ok();
 }
 

@@ -27,8 +27,11 @@ struct ScoreLaunch {
   float* scores;
   int32_t* selected;
   int32_t* selected_count;
-  uint32_t* counters;  // [Hkv], zero between calls
+  uint32_t* counters;  // [Hkv][cnt_stride], zero between calls
+  uint32_t* gmax;      // [Hkv][gmax_stride] largest key of each group of pages, or NULL: no room for them
+  int cnt_stride, gmax_stride;
   int num_kv_heads, group, max_pages, num_pages, kextra, cap, n_forced;
+  int nblk, gshift;  // workgroups per KV head, log2 of the pages per group (set by the launcher)
   bool bf16, meta_mean;
   int32_t forced[PRR_MAX_FORCED];
 };
@@ -40,8 +43,14 @@ struct PredictLaunch {
   const float* scores;
   int32_t* predicted;
   int32_t* predicted_count;
+  // scratch of the update spread over many workgroups (scores given): NULL in prr_predict
+  uint32_t* counters;  // [Hkv][cnt_stride], zero between calls
+  uint32_t* keys;      // [Hkv][max_pages] keys of the prediction
+  uint32_t* gmax;      // [Hkv][gmax_stride] largest key of each group of pages
+  int cnt_stride, gmax_stride;
   float alpha, beta, gamma;
   int num_kv_heads, max_pages, num_pages, kextra, cap, n_forced;
+  int nblk, gshift;  // workgroups per KV head, log2 of the pages per group (set by the launcher)
   int32_t forced[PRR_MAX_FORCED];
 };
 
@@ -80,10 +89,9 @@ struct RepairLaunch {
   int32_t* missed_count;
   int32_t* wasted_count;
   float* ws_o;        // [Hkv][nwork][G][128]
-  float* ws_ml;       // [Hkv][nwork][G][2]
-  uint32_t* ws_cnt;   // [2*Hkv], zero between calls
+  uint64_t* ws_ml;    // [Hkv][nwork][G] (m, l) of each unit state, zero between calls
   uint32_t* flags;    // sticky error bits
-  int num_kv_heads, group, max_pages, num_pages, num_tokens, page_size, cap, chunk, nchunks, nwork, nmerge_per_kv, mode;
+  int num_kv_heads, group, max_pages, num_pages, num_tokens, page_size, cap, chunk, nchunks, nwork, mode;
   bool bf16;
 };
 
@@ -194,10 +202,37 @@ void calibrate_grid(const float* scores, int n_traj, int n_rows, int n_blocks, c
 float pick_delta(const int32_t* context, const float* delta, const float* select_us, const float* spec_us, int n_rows,
                  int32_t query_context, int degree, float* select_est, float* spec_est);
 hipError_t launch_meta(const MetaLaunch& a, hipStream_t stream);
-hipError_t launch_score_topk(const ScoreLaunch& a, hipStream_t stream);
+// the separate kernels, per 16-bit type
+template <bool BF16>
+hipError_t launch_score_topk_t(ScoreLaunch a, hipStream_t stream);
+template <bool BF16>
+hipError_t launch_spec_attn_t(const SpecLaunch& a, hipStream_t stream);
+template <bool BF16>
+hipError_t launch_select_spec_t(ScoreLaunch a, const SpecLaunch& b, hipStream_t stream);
+template <bool BF16>
+hipError_t launch_repair_t(const RepairLaunch& a, hipStream_t stream);
+template <bool BF16>
+hipError_t launch_repair_predict_t(const RepairLaunch& a, PredictLaunch b, hipStream_t stream);
+inline hipError_t launch_score_topk(const ScoreLaunch& a, hipStream_t s) {
+  return a.bf16 ? launch_score_topk_t<true>(a, s) : launch_score_topk_t<false>(a, s);
+}
+inline hipError_t launch_spec_attn(const SpecLaunch& a, hipStream_t s) {
+  return a.bf16 ? launch_spec_attn_t<true>(a, s) : launch_spec_attn_t<false>(a, s);
+}
+inline hipError_t launch_select_spec(const ScoreLaunch& a, const SpecLaunch& b, hipStream_t s) {
+  return a.bf16 ? launch_select_spec_t<true>(a, b, s) : launch_select_spec_t<false>(a, b, s);
+}
+inline hipError_t launch_repair(const RepairLaunch& a, hipStream_t s) {
+  return a.bf16 ? launch_repair_t<true>(a, s) : launch_repair_t<false>(a, s);
+}
+inline hipError_t launch_repair_predict(const RepairLaunch& a, const PredictLaunch& b, hipStream_t s) {
+  return a.bf16 ? launch_repair_predict_t<true>(a, b, s) : launch_repair_predict_t<false>(a, b, s);
+}
+// score + select whose selecting workgroup ranks every key in registers (1024 threads)
+hipError_t launch_score_topk_block(const ScoreLaunch& a, hipStream_t stream);
+// EMA + predict with scores and scratch (many workgroups), and in one workgroup per KV head
+hipError_t launch_ema_topk(PredictLaunch a, hipStream_t stream);
 hipError_t launch_predict(const PredictLaunch& a, hipStream_t stream);
-hipError_t launch_spec_attn(const SpecLaunch& a, hipStream_t stream);
-hipError_t launch_repair(const RepairLaunch& a, hipStream_t stream);
 hipError_t launch_merge_states(int n_states, int rows, int d, const float* o, const float* m, const float* l,
                                float* out_o, float* out_m, float* out_l, hipStream_t stream);
 

@@ -60,6 +60,7 @@ extern "C" prr_status prr_score_topk_static(const prr_dims* dims, const void* q,
   hipError_t e = prr::launch_fill_zero(ptr, sizeof(uint32_t) * kScratchWords, stream);
   if (e == hipSuccess) {
     a.counters = ptr;
+    a.cnt_stride = 1;
     e = prr::launch_score_topk(a, stream);
   }
   if (e != hipSuccess) return prr::api_fail(PRR_ERR_HIP, "score_topk_static launch: %s", hipGetErrorString(e));

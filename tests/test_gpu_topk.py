@@ -1,0 +1,149 @@
+"""The selection of the separate kernels (prr_topk.h) on scores set directly, at the edges of
+its group sizes and list, in every form of the entry points that use it; the two-stream
+step's update and prediction against prr_predict; the two-stream step captured in a graph."""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from tests import gpu_support as S
+from tests.test_gpu_parity import SELECT_DISTS, _select_values
+
+pytestmark = pytest.mark.gpu
+
+
+def _score_layer(torch, vals, k, forced, cap_pages=None):
+    """A layer whose score of page p of head h is vals[h][p]: mean metadata with the value in
+    channel 0, one query head per KV head with 1 there."""
+    from paper_2606_30389_amd import runtime as R
+    hkv, n = vals.shape
+    pc = R.PathConfig(num_q_heads=hkv, num_kv_heads=hkv, page_size=32, num_tokens=n * 32, k_select=k, forced=forced,
+                      forced_in_budget=True, dtype="bf16", meta_kind="mean", gamma=0.25, max_pages=cap_pages)
+    dev = torch.device("cuda:0")
+    st = R.LayerState(pc, dev, k=torch.zeros(hkv, pc.dims().max_pages, 32, 128, dtype=torch.bfloat16, device=dev))
+    st.meta[:, :n, 0] = torch.from_numpy(vals).to(dev)
+    q = torch.zeros(hkv, 128, dtype=torch.bfloat16, device=dev)
+    q[:, 0] = 1.0
+    return pc, st, q
+
+
+# sizes around the direct list (1024, 2048), the two group sizes (8192) and the largest select
+SIZES = [(1, 1), (5, 3), (64, 63), (1023, 200), (1025, 40), (1025, 600), (2048, 256), (2049, 255), (2500, 1000),
+         (8191, 512), (8193, 1024), (16384, 256), (16384, 1024)]
+
+
+# (most distributions plant groups of hundreds of pages)
+CASES = [(d, n, k) for n, k in SIZES for d in SELECT_DISTS if n >= 700 or d in ("gauss", "constant", "tiny")]
+
+
+@pytest.mark.parametrize("dist,n,k", CASES)
+def test_score_topk_structures(dist, n, k):
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    S.log(f"score_topk {dist}: n={n} k={k}")
+    rng = np.random.default_rng(zlib.crc32(f"{dist}/{n}/{k}".encode()))
+    vals = np.stack([_select_values(dist, n, rng) for _ in range(3)])
+    for forced in ([], sorted({0, n // 2, n - 1})):
+        pc, st, q = _score_layer(torch, vals, k, forced)
+        want = [O.select_topk(vals[h].astype(np.float64), k, forced, True) for h in range(3)]
+        calls = [("workspace", lambda: st.select(q)),
+                 # a workspace with room for the arrival counters only
+                 ("counters", lambda: L.prr_score_topk(st.dims, q, st.meta, n, k, forced, True, st.scores, st.sel,
+                                                       st.sel_count, st.cap, st.workspace, 512)),
+                 ("static", lambda: L.prr_score_topk_static(st.dims, q, st.meta, n, k, forced, True, st.scores, st.sel,
+                                                            st.sel_count, st.cap))]
+        for name, call in calls:
+            st.sel.fill_(-5)
+            st.sel_count.fill_(-5)
+            call()
+            torch.cuda.synchronize()
+            for h, got in enumerate(S.lists(st)):
+                assert np.array_equal(got, want[h]), f"{name}, head {h}: {len(set(got) ^ set(want[h]))} pages differ"
+            np.testing.assert_array_equal(S.to_np(st.scores)[:, :n], vals)
+
+
+def test_score_topk_refuses_less_than_its_counters():
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    _, st, q = _score_layer(torch, np.zeros((3, 40), dtype=np.float32), 4, [])
+    with pytest.raises(L.PrrError) as e:
+        L.prr_score_topk(st.dims, q, st.meta, 40, 4, [], True, st.scores, st.sel, st.sel_count, st.cap, st.workspace, 256)
+    assert e.value.status == L.PRR_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("n,k,forced", [(1, 1, []), (250, 20, [0, 249]), (1030, 300, [3]), (2049, 128, []),
+                                        (9000, 256, [0, 8998, 8999]), (16384, 700, [])])
+def test_prefill_and_two_stream_predictions(n, k, forced):
+    """PRR_SCHED_PREFILL and PRR_SCHED_TWO_STREAM update and predict in many workgroups;
+    prr_predict, which one workgroup per KV head serves, gives the same state and lists."""
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    from paper_2606_30389_amd import runtime as R
+    S.log(f"predictions n={n} k={k}")
+    rng = np.random.default_rng(n)
+    vals = rng.standard_normal((2, n)).astype(np.float32)
+    layers = [_score_layer(torch, vals, k, forced, n + 5) for _ in range(2)]
+    (_, a, q), (_, b, _) = layers
+    stack = R.DecodeStack([a], [q], torch.device("cuda:0"))
+    spec = torch.cuda.Stream()
+    for step in range(3):
+        new = torch.from_numpy(rng.standard_normal((2, n)).astype(np.float32)).cuda()
+        for st in (a, b):
+            st.meta[:, :n, 0] = new
+        torch.cuda.synchronize()
+        stack.step(L.PRR_SCHED_TWO_STREAM if step else L.PRR_SCHED_PREFILL, torch.cuda.current_stream(), spec)
+        b.select(q)
+        b.predict()
+        b.advance()
+        torch.cuda.synchronize()
+        for name in ("level", "trend", "init_bits", "scores", "sel", "sel_count"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), (step, name)
+        assert torch.equal(a.pred_count[a.cur], b.pred_count[b.cur])
+        for h in range(2):
+            m = int(a.pred_count[a.cur][h])
+            assert torch.equal(a.pred[a.cur][h, :m], b.pred[b.cur][h, :m]), step
+
+
+def test_two_stream_step_in_a_graph():
+    """The two-stream step under capture, replayed between eager work, equals the eager step."""
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    from paper_2606_30389_amd import runtime as R
+    cfg = W.CONFIGS["glm32k"]
+    pc = S.path_config(cfg, num_pages=300)
+    st, _ = S.make_layer(cfg, pc)
+    st.build_meta()
+    _, qb = W.query_trajectory(cfg, 0, steps=5)
+    q = S.q_tensor(qb[0], pc).clone()
+    stack = R.DecodeStack([st], [q], torch.device("cuda:0"))
+    s, spec = torch.cuda.Stream(), torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    stack.step(L.PRR_SCHED_PREFILL, s)
+    torch.cuda.synchronize()
+    keep = ("level", "trend", "init_bits", "scores", "out_o32", "out_m", "out_l", "missed", "wasted")
+    state = {n: getattr(st, n).clone() for n in keep}
+    lists = [x.clone() for x in st.pred + st.pred_count]
+    cur = st.cur
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        stack.step(L.PRR_SCHED_TWO_STREAM, s, spec)
+    for t in range(1, 5):
+        results = []
+        for replay in (False, True):
+            for n in keep:
+                getattr(st, n).copy_(state[n])
+            for x, y in zip(st.pred + st.pred_count, lists):
+                x.copy_(y)
+            st.cur = cur
+            q.copy_(S.q_tensor(qb[t], pc))
+            torch.cuda.synchronize()
+            if replay:
+                graph.replay()
+            else:
+                stack.step(L.PRR_SCHED_TWO_STREAM, s, spec)
+            torch.cuda.synchronize()
+            results.append([getattr(st, n).clone() for n in keep] + [st.pred[1 - cur].clone()])
+        for x, y in zip(*results):
+            assert torch.equal(x, y)
