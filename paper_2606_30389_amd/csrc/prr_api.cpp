@@ -99,15 +99,18 @@ bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
   // the same counters on lines of their own: hundreds of workgroups of many KV heads add to them
   L.sel_pcnt = off;
   off += (size_t)hkv * kCounterStride * 4;
+  L.ema_cnt = off;
+  off += (size_t)hkv * kCounterStride * 4;
+  // the repair's words, which are zero between calls: like the counters before them they lie
+  // where no call's capacity, chunk or page count moves them, so calls of other sizes may share
+  // a workspace
+  L.rep_ml = off;
+  off = align_up(off + (size_t)hkv * (2 * PRR_MAX_CAP) * g * 8, 256);
   L.gmax_stride = div_up(d->max_pages, 4);  // (groups of at least four pages)
   L.sel_gmax = off;
   off = align_up(off + (size_t)hkv * L.gmax_stride * 4, 256);
-  L.ema_cnt = off;
-  off += (size_t)hkv * kCounterStride * 4;
   L.rep_o = off;
   off = align_up(off + (size_t)hkv * L.nwork_max * g * 128 * 4, 256);
-  L.rep_ml = off;
-  off = align_up(off + (size_t)hkv * L.nwork_max * g * 2 * 4, 256);
   // fused step: tagged scores, threshold, missed count and list, partial states
   L.nparts = 3 * L.nchunks;
   L.f_score = off;
@@ -461,7 +464,7 @@ static prr_status score_args(const prr_dims* dims, const void* q, const void* me
   if (!ws_layout(dims, cap, 1, L) || ws_bytes < L.sel_pcnt)
     return fail(PRR_ERR_WORKSPACE, "workspace of %zu bytes too small", ws_bytes);
   char* ws = static_cast<char*>(workspace);
-  const bool room = ws_bytes >= L.ema_cnt;
+  const bool room = ws_bytes >= L.rep_o;
   a.counters = reinterpret_cast<uint32_t*>(ws + (room ? L.sel_pcnt : L.sel_cnt));
   a.cnt_stride = room ? kCounterStride : 1;
   // (these regions lie ahead of every one whose place depends on the chunk; a workspace that

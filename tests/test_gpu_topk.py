@@ -147,3 +147,40 @@ def test_two_stream_step_in_a_graph():
             results.append([getattr(st, n).clone() for n in keep] + [st.pred[1 - cur].clone()])
         for x, y in zip(*results):
             assert torch.equal(x, y)
+
+
+def test_repair_calls_of_other_sizes_share_a_workspace():
+    """Serial and exact repairs of several chunk sizes in turn on one workspace: each leaves it
+    as the next call needs it."""
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    from paper_2606_30389_amd import runtime as R
+    pc = R.PathConfig(num_q_heads=8, num_kv_heads=2, page_size=16, num_tokens=300 * 16 - 3, k_select=70, dtype="f16",
+                      chunk_pages=1)
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev).manual_seed(3)
+    k, v = (torch.randn(2, 300, 16, 128, generator=g, device=dev).half() for _ in range(2))
+    st = R.LayerState(pc, dev, k=k, v=v)
+    q = torch.randn(8, 128, generator=g, device=dev).half()
+    order = torch.rand(2, 300, generator=g, device=dev).argsort(dim=-1)
+    st.sel[:] = order[:, :70].sort(dim=-1).values
+    pred = order[:, 35:105].sort(dim=-1).values.to(torch.int32).contiguous()
+    st.sel_count.fill_(70)
+    count = st.sel_count.clone()
+    results = {True: [], False: []}
+    for chunk, serial in [(8, True), (1, False), (16, False), (3, True), (8, False), (1, True), (16, False), (2, True)]:
+        S.log(f"repair chunk={chunk} serial={serial}")
+        lists = (st.sel, st.sel_count) + ((None, None) if serial else (pred, count))
+        if not serial:
+            L.prr_spec_attn(st.dims, q, st.k, st.v, None, pc.num_tokens, pred, count, st.cap, chunk, st.part_o, st.part_m,
+                            st.part_l, st.page_m)
+        for out in (st.out_o32, st.out_m, st.out_l):
+            out.fill_(float("nan"))
+        L.prr_repair(st.dims, q, st.k, st.v, None, pc.num_tokens, 300, *lists, st.cap, chunk, st.part_o, st.part_m,
+                     st.part_l, st.page_m, 0, st.out_o32, st.out_o, st.out_m, st.out_l, st.missed, st.wasted,
+                     st.workspace, st.ws_bytes)
+        torch.cuda.synchronize()
+        results[serial].append((st.out_o32.clone(), st.out_l.clone()))
+    for o, l in results[True] + results[False]:
+        assert (o - results[True][0][0]).abs().max() < 1e-4 and torch.allclose(l, results[True][0][1], rtol=1e-4)
+    assert int(st.workspace[0]) == 0  # no error flag
