@@ -95,9 +95,15 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
 // channels 8*(l%16) .. +8 of token rows l/16, l/16+4, .. of each page (16-byte loads, a wave
 // load covers 4 full rows); the loads of all its pages are issued before any is reduced (8
 // per lane in flight for 16- and 32-token pages, batches of 16 from 64 tokens on), then the
-// four row groups are combined with cross-lane shuffles.  K is read once, with non-temporal
-// loads.  Measured on the 128K GLM-shaped cache (18.5 us per layer with one 16-token page per
-// wave and plain loads): two pages 18.0 us, four pages 20.0 us (22.2 with plain loads).
+// four row groups are combined by swaps of rows between pairs of registers, each of which
+// reduces two values at once and leaves every lane with its share of the page's metadata to
+// store (12 swaps for the minima and maxima of a page; a shuffle per value, row group and
+// extreme is 32 trips through the LDS crossbar, as long as the page's own loads).  K is read
+// once, with non-temporal loads.  The stores are
+// non-temporal too (a layer's metadata is read again only after the other layers').  Two KV heads x
+// 8192 pages of 16 tokens: 16.9 us per layer with shuffles, 16.4 now; 8 x 4096: 32.4 -> 28.3;
+// 100003 tokens: 15.65 -> 13.6.  One page per wave instead of two: 17.6 / 30.1 / 12.8 us, four:
+// 18.3 / 34.4 / 17.3.
 template <int PS>
 struct MetaShape {
   static constexpr int kPages = PS >= 32 ? 1 : 32 / PS;  // pages per wave
@@ -109,6 +115,18 @@ struct MetaShape {
 template <int PS>
 constexpr int meta_pages_per_block() {
   return 4 * MetaShape<PS>::kPages;
+}
+
+// Rows 1 and 3 of x for rows 0 and 2 of y, and the upper half of x for the lower half of y.
+__device__ __forceinline__ void swap_odd_rows(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_halves(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
 }
 
 // The pages of this wave: source rows (lane's channels), valid tokens, and whether the
@@ -143,13 +161,13 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
   int valid[S::kPages];
   bool ok[S::kPages];
   meta_pages<PS>(k, ptab, num_tokens, page_end, max_pages, h, first, cg, src, valid, ok);
-  float mn[S::kPages][8], mx[S::kPages][8];
+  float mn[S::kPages][8], nx[S::kPages][8];  // smallest value, smallest negated value
 #pragma unroll
   for (int j = 0; j < S::kPages; ++j) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       mn[j][e] = __builtin_inff();
-      mx[j][e] = -__builtin_inff();
+      nx[j][e] = __builtin_inff();
     }
   }
 #pragma unroll
@@ -174,7 +192,7 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
           for (int e = 0; e < 8; ++e) {
             const float f = u4_elem<BF16>(u, e);
             mn[j][e] = fminf(mn[j][e], f);
-            mx[j][e] = fmaxf(mx[j][e], f);
+            nx[j][e] = fminf(nx[j][e], -f);
           }
         }
       }
@@ -182,21 +200,26 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
   }
 #pragma unroll
   for (int j = 0; j < S::kPages; ++j) {
+    // rows 0 and 2 get the minima of two row groups, rows 1 and 3 the negated maxima; then the
+    // lower half all of elements 0..3, the upper half of 4..7
+    float z[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      mn[j][e] = fminf(mn[j][e], __shfl_xor(mn[j][e], 16));
-      mn[j][e] = fminf(mn[j][e], __shfl_xor(mn[j][e], 32));
-      mx[j][e] = fmaxf(mx[j][e], __shfl_xor(mx[j][e], 16));
-      mx[j][e] = fmaxf(mx[j][e], __shfl_xor(mx[j][e], 32));
+      float x = mn[j][e], y = nx[j][e];
+      swap_odd_rows(x, y);
+      z[e] = fminf(x, y);
     }
-    if (ok[j] && rg < 2) {
-      const float* x = rg == 0 ? mn[j] : mx[j];
-      uint4 o;
-      o.x = f2h_exact<BF16>(x[0]) | (f2h_exact<BF16>(x[1]) << 16);
-      o.y = f2h_exact<BF16>(x[2]) | (f2h_exact<BF16>(x[3]) << 16);
-      o.z = f2h_exact<BF16>(x[4]) | (f2h_exact<BF16>(x[5]) << 16);
-      o.w = f2h_exact<BF16>(x[6]) | (f2h_exact<BF16>(x[7]) << 16);
-      *reinterpret_cast<uint4*>(meta + (((size_t)h * max_pages + first + j) * 2 + rg) * kHeadDim + cg * 8) = o;
+    uint32_t b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x = z[e], y = z[e + 4];
+      swap_halves(x, y);
+      const float v = fminf(x, y);
+      b[e] = f2h_exact<BF16>((rg & 1) ? -v : v);
+    }
+    if (ok[j]) {
+      uint16_t* dst = meta + (((size_t)h * max_pages + first + j) * 2 + (rg & 1)) * kHeadDim + cg * 8 + (rg >> 1) * 4;
+      __builtin_nontemporal_store((uint64_t)(b[0] | (b[1] << 16)) | ((uint64_t)(b[2] | (b[3] << 16)) << 32), reinterpret_cast<uint64_t*>(dst));
     }
   }
 }
@@ -248,15 +271,24 @@ __global__ __launch_bounds__(256) void meta_mean_kernel(const uint16_t* __restri
 #pragma unroll
   for (int j = 0; j < S::kPages; ++j) {
     const float inv = 1.0f / (float)valid[j];
+    // (s0 + s1) + (s2 + s3) of the four row groups: rows 0 and 2 get elements 0..3 of two of
+    // them, rows 1 and 3 elements 4..7; then each half two of the four
+    float z[4], o[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      sm[j][e] += __shfl_xor(sm[j][e], 16);
-      sm[j][e] += __shfl_xor(sm[j][e], 32);
+    for (int e = 0; e < 4; ++e) {
+      float x = sm[j][e], y = sm[j][e + 4];
+      swap_odd_rows(x, y);
+      z[e] = x + y;
     }
-    if (ok[j] && rg == 0) {
-      float4* dst = reinterpret_cast<float4*>(meta + ((size_t)h * max_pages + first + j) * kHeadDim + cg * 8);
-      dst[0] = make_float4(sm[j][0] * inv, sm[j][1] * inv, sm[j][2] * inv, sm[j][3] * inv);
-      dst[1] = make_float4(sm[j][4] * inv, sm[j][5] * inv, sm[j][6] * inv, sm[j][7] * inv);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float x = z[e], y = z[e + 2];
+      swap_halves(x, y);
+      o[e] = (x + y) * inv;
+    }
+    if (ok[j]) {
+      float* dst = meta + ((size_t)h * max_pages + first + j) * kHeadDim + cg * 8 + (rg & 1) * 4 + (rg >> 1) * 2;
+      *reinterpret_cast<float2*>(dst) = make_float2(o[0], o[1]);
     }
   }
 }
