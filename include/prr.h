@@ -408,7 +408,7 @@ prr_status prr_epoch_advance(uint32_t* epoch_dev, hipStream_t stream);
  * prediction) are averaged, then over the trajectories.  Host code, run on the CPU while
  * the device finishes the prefill; no device memory is touched.
  *   scores         host [n_traj][n_rows][n_blocks] float32 prefill score trajectories;
- *                  entries of blocks that do not exist yet at a row are never read
+ *                  entries of blocks that do not exist yet at a row have no effect
  *   form_row       host [n_blocks] int32 >= 0, the row at which each block forms (shared by
  *                  the trajectories), or NULL = every block exists from row 0
  *   k_select       |A_phi|; p_select: |P_phi| (0 = k_select)

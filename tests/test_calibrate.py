@@ -67,6 +67,28 @@ def test_calibrate_growing_blocks_and_threads():
     assert int(np.argmax(ref)) == int(np.argmax(o1)) and b1 == tuple(float(x) for x in grid[int(np.argmax(ref))])
 
 
+@pytest.mark.parametrize("k,p,drift,step", [(12, 0, 0.02, 0.0), (12, 9, 0.5, 0.25), (40, 160, 0.1, 1.0), (1, 1, 0.0, 0.0),
+                                            (30, 299, 0.3, 0.0)])
+def test_calibrate_candidate_bound(k, p, drift, step):
+    """Rows ranked through the bound kept from the row before: slow and fast drifts, scores on a
+    grid (hundreds of ties), budgets up to every block, blocks that form late over NaN entries;
+    every objective is the oracle's."""
+    L = _lib()
+    rows, blocks, growing = 24, 600, 300
+    traj = _trajectory(k + p, rows, blocks, drift)
+    if step:
+        traj = (np.round(traj / step) * step).astype(np.float32)
+    fr = np.zeros(blocks, dtype=np.int32)
+    fr[::2] = np.arange(growing) % (rows + 4)
+    for r in range(rows):
+        traj[r, fr > r] = np.nan
+    grid = np.asarray(O.THETA_GRID, dtype=np.float32)[::9]
+    _, obj = L.prr_calibrate(traj, k, grid, p_select=p, n_threads=3, form_row=fr)
+    clean = np.nan_to_num(traj.astype(np.float64))
+    ref = np.array([O.calibration_objective(clean, k, tuple(float(x) for x in th), p or None, fr) for th in grid])
+    np.testing.assert_allclose(obj, ref, rtol=0, atol=1e-12)
+
+
 def test_calibrate_formation_pins_natively():
     """The library's calibration on the hand-worked trajectories that pin the oracle."""
     from tests import oracle_pins as pins
