@@ -120,6 +120,7 @@ struct FScoreLds {
   float qbar[kHeadDim];
   float sc[kFScorePages];
   uint32_t fbits[kFScorePages / 32];
+  uint32_t win[4];  // the candidate bounds of the previous step
 };
 
 struct FSelLds {
@@ -197,7 +198,7 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
   const int pbase = blk * kFScorePages;
   const bool ema = a.schedule != 0;
   const uint16_t* q = static_cast<const uint16_t*>(a.q);
-  // wave 0 owns the filtering: EMA state of pages pbase + lane (+ 64 ...)
+  // pages pbase + lane (+ 64 ...) in the filtering waves
   constexpr int kHalves = (kFScorePages + kWave - 1) / kWave;
   float lv[kHalves], tv[kHalves];
   uint32_t bw[kHalves];
@@ -212,6 +213,8 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
   const int g16 = t >> 4, c8 = (t & 15) * 8;
   uint4 qv = make_uint4(0, 0, 0, 0);
   if (g16 < G) qv = *reinterpret_cast<const uint4*>(q + (size_t)(h * G + g16) * kHeadDim + c8);
+  uint32_t win = 0u;  // (the candidate bounds, see below)
+  if (t < 4) win = a.win[4 * h + t];
   const int cg = lane & 15, pi = lane >> 4;
   const int base = pbase + w * kFPagesPerWave + pi;
   uint4 mn[kFScoreIt], mx[kFScoreIt];
@@ -234,39 +237,35 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
       m1[it] = row[1];
     }
   }
-  // wave 0 filters: EMA state of pages pbase + lane (+ 64 ...), and the
-  // candidate bounds kept from the previous step as ratios: of A and of late pages to
-  // |q-bar|_1 (scores scale with q-bar), of the next prediction to the EMA of |q-bar|_1
-  // (the EMA keys scale with it); loaded together with the metadata
-  float r_a = 0.f, r_p = 0.f, r_l = 0.f, qe0 = 0.f;
+  // What the filtering waves need is loaded together with the metadata: the bitmap of P^t and
+  // the physical pages (late pages are listed with them), the EMA state, and the candidate
+  // bounds kept from the previous step as ratios: of A and of late pages to |q-bar|_1 (scores
+  // scale with q-bar), of the next prediction to the EMA of |q-bar|_1 (the EMA keys scale with
+  // it).  The bounds (loaded before the metadata: loads complete in issue order) go through
+  // LDS: they are read before any list is published, and the select and predict workgroups
+  // replace them only after they hold every list.
   uint32_t pw[kHalves];
-  int ph[kHalves];  // physical pages (late pages are listed with them)
+  int ph[kHalves];
 #pragma unroll
   for (int i = 0; i < kHalves; ++i) {
     pw[i] = 0u;
     ph[i] = 0;
   }
-  if (w == 0) {
-    r_a = __uint_as_float(a.win[4 * h]);
-    r_p = __uint_as_float(a.win[4 * h + 1]);
-    r_l = __uint_as_float(a.win[4 * h + 2]);
-    qe0 = __uint_as_float(a.win[4 * h + 3]);
-    if (a.late) {
+  if (w < 2 && a.late) {
 #pragma unroll
-      for (int half = 0; half < kHalves; ++half) {
-        pw[half] = a.pbits_cur[(size_t)h * nwmax + (min(pbase + 64 * half + (lane & 32), n - 1) >> 5)];
-        const int p = min(pbase + 64 * half + lane, n - 1);
-        ph[half] = a.page_table ? a.page_table[p] : p;
-      }
+    for (int half = 0; half < kHalves; ++half) {
+      pw[half] = a.pbits_cur[(size_t)h * nwmax + (min(pbase + 64 * half + (lane & 32), n - 1) >> 5)];
+      const int p = min(pbase + 64 * half + lane, n - 1);
+      ph[half] = a.page_table ? a.page_table[p] : p;
     }
-    if (ema) {
+  }
+  if (w == 3 && ema) {
 #pragma unroll
-      for (int half = 0; half < kHalves; ++half) {
-        const int p = min(pbase + 64 * half + lane, n - 1);
-        lv[half] = a.level[(size_t)h * a.max_pages + p];
-        tv[half] = a.trend[(size_t)h * a.max_pages + p];
-        bw[half] = a.init_bits[(size_t)h * nwmax + (p >> 5)];
-      }
+    for (int half = 0; half < kHalves; ++half) {
+      const int p = min(pbase + 64 * half + lane, n - 1);
+      lv[half] = a.level[(size_t)h * a.max_pages + p];
+      tv[half] = a.trend[(size_t)h * a.max_pages + p];
+      bw[half] = a.init_bits[(size_t)h * nwmax + (p >> 5)];
     }
   }
   {
@@ -276,6 +275,7 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
       for (int e = 0; e < 8; ++e) S.qpart[g][c8 + e] = u4_elem<BF16>(qv, e);
     }
     if (t < kFScorePages / 32) S.fbits[t] = 0u;
+    if (t < 4) S.win[t] = win;
     __syncthreads();
     if (t < kHeadDim) {
       float s = 0.0f;
@@ -330,7 +330,19 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
   }
   __syncthreads();
   if (t == 0) stamp(a, kStampScores);
-  if (w != 0) return;
+  // The filtering is a chain of single-wave passes, each of them issue-bound, so four waves
+  // (on the CU's four SIMDs) take one each instead of one wave all of them: 0 the late list,
+  // the longest chain after the scores; 1 the candidates of A, which the select workgroup waits
+  // for, and then the late pages' read-ahead (issued before those stores, by wave 0, it delays
+  // them: 14.71 us per layer-step instead of 14.62, 15.70 instead of 15.56 on 64-token blocks);
+  // 2 the scores; 3 the EMA update and the candidates of the next prediction, whose lists come
+  // 1.8 us sooner, so that the predict workgroup no longer ends the launch (13.1 -> 11.3 us
+  // after its start).  With the scans of cand_load and the merge's weights: 2 KV heads x 8192
+  // pages 14.87 -> 14.62 us per layer-step, x 2048 pages 13.60 -> 13.33, 8 KV heads x 4096
+  // pages 16.67 -> 16.30, the serial step at 6251 pages 16.95 -> 16.66.
+  if (w > 3 || (w == 0 && !a.late) || (w == 3 && !ema)) return;
+  const float r_a = __uint_as_float(S.win[0]), r_p = __uint_as_float(S.win[1]), r_l = __uint_as_float(S.win[2]),
+              qe0 = __uint_as_float(S.win[3]);
   const float qn = wave_sum(fabsf(S.qbar[lane]) + fabsf(S.qbar[lane + 64]));
   const float qe = qn_ema(a, qn, qe0);
   const uint32_t lo_a = score_key(r_a * qn), lo_p = score_key(r_p * qe);
@@ -344,10 +356,8 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
   uint64_t* cp_p = a.t_candp + rec_p * kFScorePages;
   int na = 0, nfa = 0, np = 0, nfp = 0, nl = 0;
   uint64_t lmask[kHalves];  // late pages of each half
-  // Late pages (not forced, not in the bitmap of P^t, key at least lo_l) are listed first:
-  // late speculation is the longer chain after the scores.  Then the candidates of A (the
-  // select workgroup waits for them), each flagged when it is also a late page, then the
-  // EMA update and the candidates of the next prediction.
+  // Late pages: not forced, not in the bitmap of P^t, key at least lo_l.  The candidates of A
+  // are flagged when they are also late pages.
   const size_t rec_l = (2 * (size_t)a.num_kv_heads + h) * a.n_score + blk;
   uint64_t* ck_l = a.t_candk + rec_l * kCandStride + 1;
   uint64_t* cp_l = a.t_candp + rec_l * kFScorePages;
@@ -357,96 +367,117 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
     lt[half] = false;
     lmask[half] = 0ull;
   }
+  if (w < 2 && a.late) {
 #pragma unroll
-  for (int half = 0; half < kHalves && a.late; ++half) {
-    const int lp = 64 * half + lane;
-    const int p = pbase + lp;
-    const bool inr = p < n && lp < kFScorePages;
-    const bool f = inr && ((S.fbits[lp >> 5] >> (lp & 31)) & 1u);
-    const uint32_t ka = score_key(S.sc[min(lp, kFScorePages - 1)]);
-    const bool late = a.late && inr && !f && ka >= lo_l && !((pw[half] >> (p & 31)) & 1u);
-    const uint64_t ml = __ballot(late);
-    lt[half] = late;
-    lmask[half] = ml;
-    if (late) {
-      // a late page is listed with its physical page in place of its key (the late
-      // workgroups only attend it; the select ranks the candidates of A)
-      const int pos = nl + lanes_below(ml);
-      put_tag(&ck_l[pos], (uint32_t)ph[half], ep);
-      put_tag(&cp_l[pos], (uint32_t)p, ep);
+    for (int half = 0; half < kHalves; ++half) {
+      const int lp = 64 * half + lane;
+      const int p = pbase + lp;
+      const bool inr = p < n && lp < kFScorePages;
+      const bool f = inr && ((S.fbits[lp >> 5] >> (lp & 31)) & 1u);
+      const uint32_t ka = score_key(S.sc[min(lp, kFScorePages - 1)]);
+      const bool late = inr && !f && ka >= lo_l && !((pw[half] >> (p & 31)) & 1u);
+      const uint64_t ml = __ballot(late);
+      lt[half] = late;
+      lmask[half] = ml;
+      if (w == 0 && late) {
+        // a late page is listed with its physical page in place of its key (the late
+        // workgroups only attend it; the select ranks the candidates of A)
+        const int pos = nl + lanes_below(ml);
+        put_tag(&ck_l[pos], (uint32_t)ph[half], ep);
+        put_tag(&cp_l[pos], (uint32_t)p, ep);
+      }
+      nl += __popcll(ml);
     }
-    nl += __popcll(ml);
-  }
-  if (a.late && lane == 0) put_tag(ck_l - 1, (uint32_t)nl, ep);
-#pragma unroll
-  for (int half = 0; half < kHalves; ++half) {
-    const int lp = 64 * half + lane;
-    const int p = pbase + lp;
-    const bool inr = p < n && lp < kFScorePages;
-    const bool f = inr && ((S.fbits[lp >> 5] >> (lp & 31)) & 1u);
-    const float sv = S.sc[min(lp, kFScorePages - 1)];
-    if (inr) {
-      // the scores, 64 pages per store instruction (whole lines)
-      scores[p] = sv;
-      put_tag(&ts[p], __float_as_uint(sv), ep);
+    if (w == 0) {
+      if (lane == 0) put_tag(ck_l - 1, (uint32_t)nl, ep);
+      return;
     }
-    const uint32_t ka = score_key(sv);
-    const bool ca = inr && (f || ka >= lo_a);
-    const bool late = lt[half];
-    const uint64_t ma = __ballot(ca), mfa = __ballot(ca && f);
-    if (ca) {
-      const int pos = na + lanes_below(ma);
-      put_tag(&ck_a[pos], ka, ep);
-      put_tag(&cp_a[pos], (uint32_t)p | (f ? 0x80000000u : 0u) | (late ? 0x40000000u : 0u), ep);
+  }
+  if (w == 1) {
+#pragma unroll
+    for (int half = 0; half < kHalves; ++half) {
+      const int lp = 64 * half + lane;
+      const int p = pbase + lp;
+      const bool inr = p < n && lp < kFScorePages;
+      const bool f = inr && ((S.fbits[lp >> 5] >> (lp & 31)) & 1u);
+      const uint32_t ka = score_key(S.sc[min(lp, kFScorePages - 1)]);
+      const bool ca = inr && (f || ka >= lo_a);
+      const uint64_t ma = __ballot(ca), mfa = __ballot(ca && f);
+      if (ca) {
+        const int pos = na + lanes_below(ma);
+        put_tag(&ck_a[pos], ka, ep);
+        put_tag(&cp_a[pos], (uint32_t)p | (f ? 0x80000000u : 0u) | (lt[half] ? 0x40000000u : 0u), ep);
+      }
+      na += __popcll(ma);
+      nfa += __popcll(mfa);
     }
-    na += __popcll(ma);
-    nfa += __popcll(mfa);
-  }
-  if (lane == 0) put_tag(ck_a - 1, (uint32_t)na | ((uint32_t)nfa << 16), ep);
-  if (a.stamps) {
-    stores_complete();
-    if (lane == 0) stamp(a, kStampCandidates);
-  }
-  // The K and V of the first late pages, one word per 64-byte line, read now: the late
-  // workgroups load them about two microseconds later and then find them in the
-  // memory-side cache.  The words only feed a check at the end of this role.
-  constexpr int kPfLoads = PS * kHeadDim * 2 / (64 * kWave);  // instructions per K (or V) of a page
-  constexpr int kPfPages = 8;
-  uint32_t pf[kPfPages][2 * kPfLoads];
-#pragma unroll
-  for (int k = 0; k < kPfPages; ++k) {
-#pragma unroll
-    for (int j = 0; j < 2 * kPfLoads; ++j) pf[k][j] = 0u;
-  }
-  if (a.readahead) {
-    const char* kh = static_cast<const char*>(a.k_cache) + (size_t)h * a.max_pages * PS * kHeadDim * 2;
-    const char* vh = static_cast<const char*>(a.v_cache) + (size_t)h * a.max_pages * PS * kHeadDim * 2;
-    uint64_t m0 = lmask[0], m1 = kHalves > 1 ? lmask[kHalves - 1] : 0ull;
+    if (lane == 0) put_tag(ck_a - 1, (uint32_t)na | ((uint32_t)nfa << 16), ep);
+    if (a.stamps) {
+      stores_complete();
+      if (lane == 0) stamp(a, kStampCandidates);
+    }
+    // The K and V of the first late pages, one word per 64-byte line, read now: the late
+    // workgroups load them about two microseconds later and then find them in the
+    // memory-side cache.  The words only feed a check at the end of this role.
+    constexpr int kPfLoads = PS * kHeadDim * 2 / (64 * kWave);  // instructions per K (or V) of a page
+    constexpr int kPfPages = 8;
+    uint32_t pf[kPfPages][2 * kPfLoads];
 #pragma unroll
     for (int k = 0; k < kPfPages; ++k) {
-      int q = -1;
-      if (m0) {
-        const int l = __builtin_ctzll(m0);
-        m0 &= m0 - 1;
-        q = __builtin_amdgcn_readlane(ph[0], l);
-      } else if (m1) {
-        const int l = __builtin_ctzll(m1);
-        m1 &= m1 - 1;
-        q = __builtin_amdgcn_readlane(ph[kHalves - 1], l);
-      }
-      if (q >= 0 && q < a.max_pages) {
-        const size_t page = (size_t)q * PS * kHeadDim * 2;
 #pragma unroll
-        for (int j = 0; j < kPfLoads; ++j) {
-          const size_t o = page + ((size_t)j * kWave + lane) * 64;
-          pf[k][j] = *reinterpret_cast<const uint32_t*>(kh + o);
-          pf[k][kPfLoads + j] = *reinterpret_cast<const uint32_t*>(vh + o);
+      for (int j = 0; j < 2 * kPfLoads; ++j) pf[k][j] = 0u;
+    }
+    if (a.readahead) {
+      const char* kh = static_cast<const char*>(a.k_cache) + (size_t)h * a.max_pages * PS * kHeadDim * 2;
+      const char* vh = static_cast<const char*>(a.v_cache) + (size_t)h * a.max_pages * PS * kHeadDim * 2;
+      uint64_t m0 = lmask[0], m1 = kHalves > 1 ? lmask[kHalves - 1] : 0ull;
+#pragma unroll
+      for (int k = 0; k < kPfPages; ++k) {
+        int q = -1;
+        if (m0) {
+          const int l = __builtin_ctzll(m0);
+          m0 &= m0 - 1;
+          q = __builtin_amdgcn_readlane(ph[0], l);
+        } else if (m1) {
+          const int l = __builtin_ctzll(m1);
+          m1 &= m1 - 1;
+          q = __builtin_amdgcn_readlane(ph[kHalves - 1], l);
+        }
+        if (q >= 0 && q < a.max_pages) {
+          const size_t page = (size_t)q * PS * kHeadDim * 2;
+#pragma unroll
+          for (int j = 0; j < kPfLoads; ++j) {
+            const size_t o = page + ((size_t)j * kWave + lane) * 64;
+            pf[k][j] = *reinterpret_cast<const uint32_t*>(kh + o);
+            pf[k][kPfLoads + j] = *reinterpret_cast<const uint32_t*>(vh + o);
+          }
         }
       }
     }
+    uint32_t px = 0u;
+#pragma unroll
+    for (int k = 0; k < kPfPages; ++k) {
+#pragma unroll
+      for (int j = 0; j < 2 * kPfLoads; ++j) px ^= pf[k][j];
+    }
+    if (px == ep * 2654435761u + 0x9e3779b9u) atomicOr(a.flags, 0u);  // (no effect when it holds)
+    return;
   }
-  if (!ema) return;
-  // ... then the EMA update of Eq. (3) and the candidates of the next prediction
+  if (w == 2) {
+#pragma unroll
+    for (int half = 0; half < kHalves; ++half) {
+      const int lp = 64 * half + lane;
+      const int p = pbase + lp;
+      if (p < n && lp < kFScorePages) {
+        // the scores, 64 pages per store instruction (whole lines)
+        const float sv = S.sc[lp];
+        scores[p] = sv;
+        put_tag(&ts[p], __float_as_uint(sv), ep);
+      }
+    }
+    return;
+  }
+  // the EMA update of Eq. (3) and the candidates of the next prediction
 #pragma unroll
   for (int half = 0; half < kHalves; ++half) {
     const int lp = 64 * half + lane;
@@ -487,13 +518,6 @@ __device__ __forceinline__ void role_score(const FusedLaunch& a, uint32_t ep, in
     nfp += __popcll(mfp);
   }
   if (lane == 0) put_tag(ck_p - 1, (uint32_t)np | ((uint32_t)nfp << 16), ep);
-  uint32_t px = 0u;
-#pragma unroll
-  for (int k = 0; k < kPfPages; ++k) {
-#pragma unroll
-    for (int j = 0; j < 2 * kPfLoads; ++j) px ^= pf[k][j];
-  }
-  if (px == ep * 2654435761u + 0x9e3779b9u) atomicOr(a.flags, 0u);  // (no effect when it holds)
 }
 
 // ------------------------------------------------------------------------ shared select pieces
@@ -849,13 +873,18 @@ __device__ __forceinline__ FCand cand_load(const FusedLaunch& a, uint32_t ep, in
       __builtin_amdgcn_s_sleep(2);
       if (it == kFSpin - 1 && lane == 0) atomicOr(a.flags, kFlagSpinTimeout);
     }
-#pragma unroll
-    for (int k = 0; k < L2; ++k) {
-      const int li = lane + kWave * k;
-      if (li < nS) {
-        cnt[li] = (int)((uint32_t)v[k] & 0xffffu);
-        fcnt[li] = (int)((uint32_t)v[k] >> 16);
-      }
+    // lane l holds list l's count: the offsets follow at once, with no barrier in between
+    const bool li = lane < nS;
+    const int cw = li ? (int)((uint32_t)v[0] & 0xffffu) : 0;
+    const int incl = wave_inclusive_scan(cw);
+    const int ft = wave_isum(li ? (int)((uint32_t)v[0] >> 16) : 0);
+    if (li) {
+      cnt[lane] = cw;
+      off[lane] = incl - cw;
+    }
+    if (lane == kWave - 1) {
+      tot[0] = incl;
+      tot[1] = ft;
     }
   }
   for (int it = 0; POLL_ALL && mine && it < kFSpin; ++it) {
@@ -883,36 +912,23 @@ __device__ __forceinline__ FCand cand_load(const FusedLaunch& a, uint32_t ep, in
   }
   __syncthreads();
   const int nc = mine ? cnt[wg] : 0;
-  if (w == 0) {
-    // lane l holds lists L2 l .. L2 l + L2 - 1 (consecutive, so the offsets follow a scan)
-    int cw[L2], sum = 0, fs = 0;
-#pragma unroll
-    for (int k = 0; k < L2; ++k) {
-      const int li = L2 * lane + k;
-      cw[k] = li < nS ? cnt[li] : 0;
-      sum += cw[k];
-      fs += li < nS ? fcnt[li] : 0;
-    }
-    const int incl = wave_inclusive_scan(sum);
-    int o = incl - sum;
-#pragma unroll
-    for (int k = 0; k < L2; ++k) {
-      const int li = L2 * lane + k;
-      if (li < nS) off[li] = o;
-      o += cw[k];
-    }
-    const int ft = wave_isum(fs);
-    if (lane == kWave - 1) {
-      tot[0] = incl;
-      tot[1] = ft;
-    }
-  }
-  __syncthreads();
   FCand r;
-  r.total = tot[0];
-  r.nforced = tot[1];
+  int o;
+  static_assert(L2 == 1, "a lane per list");
+  if (POLL_ALL) {
+    // every wave scans the counts for itself: no second barrier
+    const bool li = lane < nS;
+    const int cw = li ? cnt[lane] : 0;
+    const int incl = wave_inclusive_scan(cw);
+    r.total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    r.nforced = __builtin_amdgcn_readfirstlane(wave_isum(li ? fcnt[lane] : 0));
+    o = __shfl(incl - cw, wg);
+  } else {
+    r.total = tot[0];
+    r.nforced = tot[1];
+    o = off[min(wg, nS - 1)];
+  }
   if (mine && r.total <= kCandMax) {
-    const int o = off[wg];
     if (POLL_ALL) {
       // the poll above only ended once every one of these slots below the count was
       // from this epoch
@@ -1916,17 +1932,23 @@ __device__ __forceinline__ void role_merge(const FusedLaunch& a, uint32_t ep, in
   __syncthreads();
   if (t < kHeadDim) {
     const int c = t;
-    float M = kNegInf;
+    // lane i computes the weight of wave i % 8, and every lane reads the eight from there
+    const int ww8 = lane & (kFW - 1);
+    float part[kFW];
 #pragma unroll
-    for (int ww = 0; ww < kFW; ++ww)
-      if (L.red[1][ww] > 0.0f) M = fmaxf(M, L.red[0][ww]);
+    for (int ww = 0; ww < kFW; ++ww) part[ww] = L.acc[ww][c];
+    const float lw = L.red[1][ww8], mw = lw > 0.0f ? L.red[0][ww8] : kNegInf;
+    float M = mw;
+    M = fmaxf(M, dpp_f32<kDppXor1>(M));
+    M = fmaxf(M, dpp_f32<kDppXor2>(M));
+    M = fmaxf(M, dpp_f32<kDppHalfMirror>(M));
+    const float f = lw > 0.0f ? exp2f((mw - M) * kLog2e) : 0.0f;
+    const float lf = lw * f;
     float Lsum = 0.0f, sum = 0.0f;
 #pragma unroll
     for (int ww = 0; ww < kFW; ++ww) {
-      const float lw = L.red[1][ww];
-      const float f = lw > 0.0f ? exp2f((L.red[0][ww] - M) * kLog2e) : 0.0f;
-      Lsum += lw * f;
-      sum += L.acc[ww][c] * f;
+      Lsum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lf), ww));
+      sum += part[ww] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), ww));
     }
     const float o = Lsum > 0.0f ? sum / Lsum : 0.0f;
     const size_t row = (size_t)h * G + qn;

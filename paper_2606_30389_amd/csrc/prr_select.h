@@ -490,8 +490,8 @@ namespace prr {
 // The threshold of the same exact top-K for at most 2 * NT keys, two per thread, without
 // gathering them into one wave: every pass builds the histogram of the current key range
 // with LDS atomics, scans it (four bins per thread, DPP prefix within the wave, wave
-// totals through LDS) and keeps the bin holding the wanted rank, until that bin holds a
-// single key or a single value.  The bins of `hist` must be zero on entry (they are left
+// totals through LDS) and keeps the bin holding the wanted rank, until all of that bin is
+// taken or it holds a single value.  T is then any key that separates the selection.  The bins of `hist` must be zero on entry (they are left
 // nonzero).
 
 struct BSelLds {
@@ -596,18 +596,15 @@ __device__ __forceinline__ SelThreshold bsel_threshold(const uint32_t (&key)[2],
     const uint32_t nlo = lo + ((uint32_t)bstar << shift);
     hi = (uint32_t)min((uint64_t)hi, (uint64_t)nlo + ((1ull << shift) - 1ull));
     lo = nlo;
-    if (shift == 0) break;
-    if (cbin == 1) {
-      // the single key of the bin is T: its holder publishes it
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        if (cand[j] && key[j] >= lo && key[j] <= hi) S.res[3] = (int)key[j];
-      __syncthreads();
-      r.T = (uint32_t)S.res[3];
+    if (rank == cbin) {
+      // the whole bin is taken (mostly its only key): its lower edge separates the selection as
+      // the rank-th key itself would, and no tie is cut
+      r.T = lo;
       r.need_eq = rank;
-      r.eq_total = 1;
+      r.eq_total = cbin;
       return r;
     }
+    if (shift == 0) break;
     if (cbin <= kWave) {
       // Few keys in the bin that holds rank K: they go to LDS (the histogram is read no
       // more) and one wave ranks them, instead of another histogram pass.  T is the

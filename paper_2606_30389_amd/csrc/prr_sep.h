@@ -84,8 +84,12 @@ __device__ __forceinline__ void role_score_topk(const ScoreLaunch& a, int blk, i
   }
   __syncthreads();
   if (t < kHeadDim) {
-    float s = 0.0f;
-    for (int gg = 0; gg < G; ++gg) s += S.qpart[gg][t];
+    // (loads issued together; s is never -0, so adding 0 past the last head changes nothing)
+    float x[16], s = 0.0f;
+#pragma unroll
+    for (int gg = 0; gg < 16; ++gg) x[gg] = S.qpart[gg][t];
+#pragma unroll
+    for (int gg = 0; gg < 16; ++gg) s += gg < G ? x[gg] : 0.0f;
     S.qbar[t] = s / (float)G;
   }
   __syncthreads();
