@@ -1,4 +1,4 @@
-"""Two-stream decode-step runtime over the C ABI (device memory and streams via torch).
+"""Decode-step runtime over the C ABI (device memory and streams via torch).
 
 Per layer and decode step t (Fig. 1; Section 4):
 
