@@ -26,6 +26,7 @@ constexpr int kTopkThreads = 256;
 constexpr int kTopkWaves = kTopkThreads / kWave;
 constexpr int kTopkLog2Bins = 10;
 constexpr int kTopkBins = 1 << kTopkLog2Bins;
+constexpr int kTopkPasses = (32 + kTopkLog2Bins - 1) / kTopkLog2Bins;
 constexpr int kTopkSmall = 64;      // keys of the boundary bin ranked directly by one wave
 constexpr int kTopkSeg = 512;       // list entries of a wave
 constexpr int kTopkEntRegs = kTopkSeg / kWave;  // of a lane
@@ -68,7 +69,8 @@ __device__ __forceinline__ float topk_value(uint32_t k) {
 }
 
 // One wave: the bin (from the top) of `hist` that holds rank `rank`, the count above it and
-// its own count, to res[0..2].
+// its own count, to res[0..2].  Where fewer keys than that were counted (see rank_keys): the
+// lowest bin.
 template <int BINS>
 __device__ __forceinline__ void scan_bins(const uint32_t* hist, int rank, int* res) {
   constexpr int PL = BINS / kWave;  // bins per lane
@@ -84,13 +86,13 @@ __device__ __forceinline__ void scan_bins(const uint32_t* hist, int rank, int* r
   const int incl = wave_inclusive_scan(sum);
   const int excl = incl - sum;
   const uint64_t hit = __ballot(excl < rank && rank <= incl);
-  const int ls = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
+  const int ls = hit != 0ull ? __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1) : kWave - 1;
   const int ex = __builtin_amdgcn_readlane(excl, ls);
   const int lbase = BINS - PL * (ls + 1);
   const int cj = lane < PL ? (int)hist[lbase + PL - 1 - lane] : 0;
   const int cinc = wave_inclusive_scan(cj);
   const uint64_t hit2 = __ballot(lane < PL && ex + cinc >= rank);
-  const int js = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit2) - 1);
+  const int js = hit2 != 0ull ? __builtin_amdgcn_readfirstlane(__ffsll((long long)hit2) - 1) : PL - 1;
   if (lane == js) {
     res[0] = lbase + PL - 1 - js;
     res[1] = ex + cinc - cj;
@@ -158,6 +160,10 @@ __device__ __forceinline__ void topk_range(const EACH& each, const IN& in, uint3
 // all of them in [lo, hi], at least `rank` over the workgroup), narrowed until it holds at
 // most `slack` keys or one value.  The histogram is zero on entry and, behind the caller's
 // next barrier, on return.
+// Both holds only as long as the keys and the group maxima in memory belong together; where a
+// caller lets them be overwritten, the result is unspecified but this still ends: a pass over
+// key bits leaves at most 2^-10 of its range (kTopkPasses cover 32 bits), and a bin that holds
+// none of the keys ends it, as its range is empty.
 template <class EACH>
 __device__ __forceinline__ TopkBin rank_keys(const EACH& each, int rank, int slack, uint32_t lo, uint32_t hi,
                                              TopkLds& S) {
@@ -184,7 +190,7 @@ __device__ __forceinline__ TopkBin rank_keys(const EACH& each, int rank, int sla
     topk_range(each, [&](uint32_t k) { return b.bin_of(k) == b.bin; }, b.lo, b.hi, S);
     b.narrowed = true;
   }
-  while (b.count > slack && b.lo != b.hi) {
+  for (int pass = 0; pass < kTopkPasses && b.count > slack && b.lo < b.hi; ++pass) {
     const uint32_t klo = b.lo, khi = b.hi;
     const int bits = 32 - __clz(khi - klo), shift = bits > kTopkLog2Bins ? bits - kTopkLog2Bins : 0;
     each([&](uint32_t k) {
@@ -382,19 +388,22 @@ __device__ __forceinline__ void topk_select(int n, int gshift, int kextra, const
 #pragma unroll
       for (int r = 0; r < kTopkEntRegs; ++r) {
         if (r * kWave >= c) break;
-        if ((uint32_t)ep[r] < (uint32_t)kTopkForced && b.in(ek[r]))
-          S.small[atomicAdd(&S.nsmall, 1)] = ek[r];
+        if ((uint32_t)ep[r] < (uint32_t)kTopkForced && b.in(ek[r])) {
+          const int i = atomicAdd(&S.nsmall, 1);
+          if (i < kTopkSmall) S.small[i] = ek[r];
+        }
       }
       __syncthreads();
       if (w == 0) {
-        const uint32_t kx = S.small[lane < b.count ? lane : 0];
+        const int nb = min(b.count, kTopkSmall);
+        const uint32_t kx = S.small[lane < nb ? lane : 0];
         int gt = 0, ge = 0;
-        for (int x = 0; x < b.count; ++x) {
+        for (int x = 0; x < nb; ++x) {
           const uint32_t ky = (uint32_t)__builtin_amdgcn_readlane((int)kx, x);
           gt += ky > kx ? 1 : 0;
           ge += ky >= kx ? 1 : 0;
         }
-        const uint64_t hit = __ballot(lane < b.count && gt < rank && rank <= ge);
+        const uint64_t hit = __ballot(lane < nb && gt < rank && rank <= ge);
         const int ls = __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
         if (lane == ls) {
           S.res[3] = (int)kx;
