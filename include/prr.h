@@ -99,17 +99,26 @@ typedef struct {
 const char* prr_status_string(prr_status status);
 const char* prr_last_error(void);
 
-/* Bytes of workspace used by prr_score_topk, prr_repair and the fused schedules of
- * prr_decode_step for lists of at most `cap` pages and speculation chunks of
- * `chunk_pages` pages.  The workspace holds disjoint regions (selection counters,
- * repair counters, repair partial states, the fused step's tagged hand-off buffers);
- * one prr_score_topk and one prr_repair may use the same workspace at the same time,
- * two calls of the same entry point may not.  Returns 0 if the arguments are invalid. */
+/* Bytes of workspace used by prr_score_topk, prr_repair and prr_decode_step for lists of at
+ * most `cap` pages and speculation chunks of `chunk_pages` pages.  The workspace holds error
+ * flags, arrival counters and disjoint regions: those of the selection (its counters, the
+ * largest key of each group of pages), of the EMA update and prediction of PRR_SCHED_PREFILL
+ * and PRR_SCHED_TWO_STREAM (counters, keys, group maxima), of the repair (states of its work
+ * units) and of the fused step (tagged hand-off buffers).  One prr_score_topk and one
+ * prr_repair of the same dims, cap and chunk_pages may use the same workspace at the same time,
+ * two calls of the same entry point may not, nor may prr_decode_step and any other call.
+ * Calls of any dims (up to 4096 KV heads), cap and chunk_pages may use one workspace in turn if
+ * it is large enough for each, the fused schedules excepted: they recognise their data by the
+ * step's epoch, so before a fused step a workspace that calls of other dims, cap or chunk_pages
+ * have used has to be zeroed again.  Returns 0 if the arguments are invalid. */
 size_t prr_workspace_size(const prr_dims* dims, int32_t cap, int32_t chunk_pages);
 
 /* Zero a workspace (device, `bytes` long, 256-byte aligned) with a fill kernel on
  * `stream`.  Required once before first use; every call leaves its counters at zero
- * again when it finishes. */
+ * again when it finishes.  Word 0 holds error flags that calls set and never clear:
+ * bit 0 a page-list entry or page-table entry out of range (skipped), bit 1 a hand-off
+ * inside a launch that was given up after a bounded wait.  After bit 1 the results of
+ * that call are invalid and the workspace has to be zeroed again before its next use. */
 prr_status prr_workspace_init(void* workspace, size_t bytes, hipStream_t stream);
 
 /* Size in floats of the speculation output of prr_spec_attn for lists of at most

@@ -7,6 +7,7 @@
 #include <stddef.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 
 #include "prr.h"
@@ -78,12 +79,17 @@ prr_status check_ptr(const void* p, const char* name, size_t align) {
     if (_s != PRR_OK) return _s;   \
   } while (0)
 
-constexpr int kCounterStride = 64;  // words between the arrival counters of two KV heads
+// What has to be zero when a call is given its workspace (the arrival counters) lies in blocks
+// of this many words at its front, where no head shape, capacity, chunk size or page count moves
+// it, so calls of any of them may use one workspace in turn.  (A shape of more KV heads has
+// longer blocks.)
+constexpr int kFixedWords = 4096;
+constexpr int kCounterStride = 64;  // words between the arrival counters of two KV heads (a line and more)
 
 struct WsLayout {
-  size_t flags, sel_cnt, sel_pcnt, sel_gmax, ema_cnt, rep_o, rep_ml, f_score, f_thr, f_mcnt, f_mlist, f_part, f_parto, f_candk,
+  size_t flags, sel_cnt, sel_cnt_end, sel_pcnt, sel_gmax, ema_cnt, rep_o, rep_ml, f_score, f_thr, f_mcnt, f_mlist, f_part, f_parto, f_candk,
       f_candp, f_pkey, f_win, f_lcnt, f_pbits, ema_gmax, ema_keys, total;
-  int nchunks, nwork_max, nparts, gmax_stride;
+  int nchunks, nwork_max, nparts, gmax_stride, cnt_stride;
 };
 
 bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
@@ -94,21 +100,23 @@ bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
   size_t off = 0;
   L.flags = off;
   off += 256;
+  // arrival counters of a selection whose workspace holds nothing else
   L.sel_cnt = off;
-  off = align_up(off + (size_t)hkv * 4, 256);
-  // the same counters on lines of their own: hundreds of workgroups of many KV heads add to them
+  L.sel_cnt_end = align_up(off + (size_t)hkv * 4, 256);
+  const size_t kv_words = std::max(kFixedWords, hkv);
+  off = align_up(off + kv_words * 4, 256);
+  // the same counters apart from each other: hundreds of workgroups of many KV heads add to them
+  L.cnt_stride = kCounterStride;
+  while (L.cnt_stride > 1 && (int64_t)hkv * L.cnt_stride > kFixedWords) L.cnt_stride /= 2;
   L.sel_pcnt = off;
-  off += (size_t)hkv * kCounterStride * 4;
+  off = align_up(off + kv_words * 4, 256);
   L.ema_cnt = off;
-  off += (size_t)hkv * kCounterStride * 4;
-  // the repair's words, which are zero between calls: like the counters before them they lie
-  // where no call's capacity, chunk or page count moves them, so calls of other sizes may share
-  // a workspace
-  L.rep_ml = off;
-  off = align_up(off + (size_t)hkv * (2 * PRR_MAX_CAP) * g * 8, 256);
+  off = align_up(off + kv_words * 4, 256);
   L.gmax_stride = div_up(d->max_pages, 4);  // (groups of at least four pages)
   L.sel_gmax = off;
   off = align_up(off + (size_t)hkv * L.gmax_stride * 4, 256);
+  L.rep_ml = off;
+  off = align_up(off + (size_t)hkv * L.nwork_max * g * 2 * 8, 256);
   L.rep_o = off;
   off = align_up(off + (size_t)hkv * L.nwork_max * g * 128 * 4, 256);
   // fused step: tagged scores, threshold, missed count and list, partial states
@@ -461,14 +469,13 @@ static prr_status score_args(const prr_dims* dims, const void* q, const void* me
                              selected_count, cap, a));
   PRR_TRY(check_ptr(workspace, "workspace", 256));
   WsLayout L;
-  if (!ws_layout(dims, cap, 1, L) || ws_bytes < L.sel_pcnt)
+  if (!ws_layout(dims, cap, 1, L) || ws_bytes < L.sel_cnt_end)
     return fail(PRR_ERR_WORKSPACE, "workspace of %zu bytes too small", ws_bytes);
   char* ws = static_cast<char*>(workspace);
-  const bool room = ws_bytes >= L.rep_o;
+  const bool room = ws_bytes >= L.rep_ml;
   a.counters = reinterpret_cast<uint32_t*>(ws + (room ? L.sel_pcnt : L.sel_cnt));
-  a.cnt_stride = room ? kCounterStride : 1;
-  // (these regions lie ahead of every one whose place depends on the chunk; a workspace that
-  // holds the counters alone does, at the cost of a slower select)
+  a.cnt_stride = room ? L.cnt_stride : 1;
+  // (a workspace that holds the counters alone does, at the cost of a slower select)
   a.gmax = room ? reinterpret_cast<uint32_t*>(ws + L.sel_gmax) : nullptr;
   a.gmax_stride = L.gmax_stride;
   return ok();
@@ -539,7 +546,7 @@ prr_status prr_predict(const prr_dims* dims, float* ema_level, float* ema_trend,
 static void predict_scratch(void* workspace, const WsLayout& L, prr::PredictLaunch& a) {
   char* ws = static_cast<char*>(workspace);
   a.counters = reinterpret_cast<uint32_t*>(ws + L.ema_cnt);
-  a.cnt_stride = kCounterStride;
+  a.cnt_stride = L.cnt_stride;
   a.keys = reinterpret_cast<uint32_t*>(ws + L.ema_keys);
   a.gmax = reinterpret_cast<uint32_t*>(ws + L.ema_gmax);
   a.gmax_stride = L.gmax_stride;
@@ -664,6 +671,8 @@ static prr_status repair_args(const prr_dims* dims, const void* q, const void* k
   char* ws = static_cast<char*>(workspace);
   a.ws_o = reinterpret_cast<float*>(ws + L.rep_o);
   a.ws_ml = reinterpret_cast<uint64_t*>(ws + L.rep_ml);
+  static std::atomic<uint32_t> count{0};  // (over all threads; a replayed graph keeps its call's tag)
+  a.tag = prr::kRepairTag + count.fetch_add(1, std::memory_order_relaxed) % prr::kRepairTags;
   a.flags = reinterpret_cast<uint32_t*>(ws + L.flags);
   a.num_kv_heads = dims->num_kv_heads;
   a.group = g;

@@ -69,6 +69,8 @@ struct SpecLaunch {
   bool bf16;
 };
 
+constexpr uint32_t kRepairTag = 0xffc00001u, kRepairTags = 0x3ffffeu;
+
 struct RepairLaunch {
   const void* q;
   const void* k_cache;
@@ -89,8 +91,11 @@ struct RepairLaunch {
   int32_t* missed_count;
   int32_t* wasted_count;
   float* ws_o;        // [Hkv][nwork][G][128]
-  uint64_t* ws_ml;    // [Hkv][nwork][G] (m, l) of each unit state, zero between calls
+  uint64_t* ws_ml;    // [Hkv][nwork][G][2] m and l of each unit state, each with the call's tag above it
   uint32_t* flags;    // sticky error bits
+  uint32_t tag;       // of this call: kRepairTag + a count, a word that nothing else kept in a workspace has as
+                      // the upper half of 64 aligned bits (as a float or score key a NaN's with a payload, as a
+                      // step's epoch one that no counting reaches)
   int num_kv_heads, group, max_pages, num_pages, num_tokens, page_size, cap, chunk, nchunks, nwork, mode;
   bool bf16;
 };

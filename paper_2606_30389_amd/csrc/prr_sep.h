@@ -535,12 +535,14 @@ __global__ __launch_bounds__(256) void select_spec_kernel(const ScoreLaunch a, c
 //   comes from the per-page maxima of the speculation); otherwise attend the chunk's
 //   pages of A afresh.  Either way the unit's state replaces chunk c.
 // A unit's outputs are published with device-coherent stores and, once those have completed,
-// one word per query head that holds (m, l).  That word is never zero for a state (the empty
-// one has m = -inf), so a merge workgroup waits (bounded spin) for the words of its head to
-// become non-zero, reads the outputs, and puts the words back to zero for the next call: no
-// counter between the last state and the merge.  Serial call, 128 of the 32-token
-// pages of 8 KV heads: 17.7 -> 10.7 us (without the plan, the unit counter and a merge of two
-// heads per workgroup).
+// two words per query head: m and l, each below the call's tag.  A merge workgroup waits
+// (bounded spin) for the tag on the words of its head, reads the outputs, and clears the words:
+// no counter between the last state and the merge.  Nothing else kept in a workspace looks like
+// a tag (see RepairLaunch), so the words need not hold anything in particular before a call and
+// may lie where calls of other shapes keep other data, and a state that a merge gave up waiting
+// for does not pass for one of a later call.  Serial call, 128 of the 32-token pages of 8 KV
+// heads: 17.7 -> 10.7 us (without the plan, the unit counter and a merge of two heads per
+// workgroup).
 
 constexpr float kMaxWastedShare = 0.875f;
 constexpr int kSpinLimit = 1 << 24;
@@ -626,15 +628,15 @@ __device__ __forceinline__ void publish_unit(const RepairLaunch& a, int h, int u
     __hip_atomic_store(dst + i, reinterpret_cast<const uint64_t*>(tile)[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   stores_complete();
   __syncthreads();
-  if (t < G) {
-    uint64_t v = ((uint64_t)__float_as_uint(L.wl[0][t]) << 32) | __float_as_uint(L.wm[0][t]);
-    if (v == 0) v = __float_as_uint(-__builtin_inff());
-    __hip_atomic_store(a.ws_ml + row0 + t, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (t < 2 * G) {
+    const float x = (t & 1) ? L.wl[0][t >> 1] : L.wm[0][t >> 1];
+    __hip_atomic_store(a.ws_ml + row0 * 2 + t, ((uint64_t)a.tag << 32) | __float_as_uint(x), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 // The unit states of query head g of KV head h into a merge wave's running state: waits for
-// the words, then reads the outputs and clears the words.
+// the words with this call's tag, then reads the outputs and clears the words.
 __device__ __forceinline__ void fold_units(const RepairLaunch& a, int h, int g, int n, int w, float& M, float& L,
                                            float& ax, float& ay) {
   const int lane = lane_id();
@@ -642,21 +644,27 @@ __device__ __forceinline__ void fold_units(const RepairLaunch& a, int h, int g, 
   fold_states(
       n, w,
       [&](int u, bool mine, float& m, float& l) {
-        uint64_t* p = a.ws_ml + row0 + (size_t)u * a.group;
-        uint64_t v = 0;
+        uint64_t* p = a.ws_ml + (row0 + (size_t)u * a.group) * 2;
+        uint64_t vm = 0, vl = 0;
+        bool ready = false;
         int it = 0;
         for (;;) {
-          v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (__ballot(v == 0) == 0ull) break;
+          vm = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          vl = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ready = (uint32_t)(vm >> 32) == a.tag && (uint32_t)(vl >> 32) == a.tag;
+          if (__ballot(!ready) == 0ull) break;
           __builtin_amdgcn_s_sleep(1);
           if (++it > kSpinLimit) {
             if (lane == 0) atomicOr(a.flags, kFlagSpinTimeout);
             break;
           }
         }
-        if (mine) __hip_atomic_store(p, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        m = __uint_as_float((uint32_t)v);
-        l = __uint_as_float((uint32_t)(v >> 32));
+        if (mine) {
+          __hip_atomic_store(p, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(p + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        m = __uint_as_float((uint32_t)vm);
+        l = ready ? __uint_as_float((uint32_t)vl) : 0.0f;
         // the outputs are loaded only now that their state is complete
         asm volatile("" ::: "memory");
       },
