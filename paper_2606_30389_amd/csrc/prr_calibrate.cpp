@@ -142,6 +142,26 @@ void row_set(const float* scores, int T, int N, const int32_t* born, int k, int 
   }                                                                    \
   return m;
 
+// A key that at least `rank` and little more of the sampled keys reach, or the smallest of them
+// (by halving the range: nth_element takes five times as long).
+#define PRR_SAMPLE_BODY                                                \
+  int32_t lo = key[0], hi = key[0];                                    \
+  for (int i = 0; i < n; ++i) {                                        \
+    lo = lo < key[i] ? lo : key[i];                                    \
+    hi = hi > key[i] ? hi : key[i];                                    \
+  }                                                                    \
+  while (lo < hi) {                                                    \
+    const int32_t mid = (int32_t)(((int64_t)lo + hi + 1) >> 1);        \
+    int c = 0;                                                         \
+    for (int i = 0; i < n; ++i) c += key[i] >= mid ? 1 : 0;            \
+    if (c < rank) hi = mid - 1;                                        \
+    else lo = mid;                                                     \
+    if (c >= rank && c <= rank + rank / 8) break;                      \
+  }                                                                    \
+  return lo;
+
+PRR_VECTOR int32_t sample_bound_avx2(const int32_t* key, int n, int rank) { PRR_SAMPLE_BODY }
+int32_t sample_bound_base(const int32_t* key, int n, int rank) { PRR_SAMPLE_BODY }
 PRR_VECTOR void keys_avx2(const double* level, const double* trend, double gamma, int n, int32_t* key) { PRR_KEYS_BODY }
 void keys_base(const double* level, const double* trend, double gamma, int n, int32_t* key) { PRR_KEYS_BODY }
 PRR_VECTOR void ema_avx2(const float* row, double alpha, double beta, int n, double* level, double* trend) { PRR_EMA_BODY }
@@ -158,6 +178,8 @@ bool have_avx2() {
 #endif
 }
 
+constexpr int kSampled = 512;  // keys sampled per row
+
 inline uint32_t ranked(int32_t key) { return (uint32_t)key ^ 0x80000000u; }  // as key_of orders them
 
 // Eq. (4) for one theta over B trajectories of T rows of N scores, averaged over B.  Block
@@ -167,10 +189,14 @@ inline uint32_t ranked(int32_t key) { return (uint32_t)key ^ 0x80000000u; }  // 
 // prediction) are averaged.
 //
 // The time goes to passes over all blocks, so a row makes three plain ones (keys, collect,
-// EMA) and ranks few: a bound kept from the row before, the key of rank 2p there, leaves about
-// 2p candidates to order exactly.  Rows where fewer than p or more than 8p reach it, and the
-// first one, rank every block by top_k.  64 rows x 8192 blocks, 80 grid points on 16 threads:
-// 13.5 ms with one scalar pass that ranked every block of every row, 4.3 ms now.
+// EMA) and ranks few: keys taken at a stride give a bound that about 2p blocks reach, and those
+// are ordered exactly.  Rows where fewer than p or more than a quarter of the blocks reach it,
+// and budgets too large for that, rank every block by top_k.  The bound is each row's own: the
+// scores of a row move as a whole with the query, so a key kept from the row before (as it was
+// once) missed the range on half of the rows of real trajectories.  64 rows x 8192 blocks, 80
+// grid points, 8 threads; one scalar pass that ranks every block, a bound from the row before,
+// this: rows of fixed mean 56-71, 22-27, 23-25 ms; Quest scores of 16 query heads (correlation 0.95 between rows)
+// 61-75, 65-70, 22; of 4 (0.85) 64-72, 82-90, 24.
 double objective(const float* scores, int B, int T, int N, const int32_t* born, const std::vector<int>& late,
                  const RowSets& R, int p, const float theta[3]) {
   const double alpha = theta[0], beta = theta[1], gamma = theta[2];
@@ -182,14 +208,18 @@ double objective(const float* scores, int B, int T, int N, const int32_t* born, 
   std::vector<int> ci(N + 32);
   std::vector<uint64_t> order;
   TopK tk;
+  // the sampled keys, and the rank among them that p blocks reach, four standard deviations
+  // and two more on top
+  const int stride = std::max(1, N / kSampled), n_sample = N / stride;
+  const double mean = (double)p * n_sample / N;
+  const int srank = (int)std::min(2.0 * kSampled, mean + 4.0 * sqrt(mean) + 2.0);
+  std::vector<int32_t> sample(n_sample);
   double sum_b = 0.0;
   for (int b = 0; b < B; ++b) {
     const float* traj = scores + (size_t)b * T * N;
     // `late` holds the blocks that form after row 0, by row; those up to `formed` have
     size_t formed = 0;
     int nhas = 0;
-    bool bounded = false;
-    int32_t bound = 0;
     double sum_t = 0.0;
     int rows = 0;
     for (int phi = 0; phi < T; ++phi) {
@@ -199,9 +229,14 @@ double objective(const float* scores, int B, int T, int N, const int32_t* born, 
         for (size_t j = formed; j < late.size(); ++j) key[late[j]] = std::numeric_limits<int32_t>::min();
         int m = -1;
         std::fill(inP.begin(), inP.end(), 0);
-        if (bounded && p > 0 && p < nhas) {
-          m = (vec ? collect_avx2 : collect_base)(key.data(), N, bound, ci.data());
-          if (m < p || m > 8 * (int64_t)p) m = -1;
+        if (srank < n_sample / 2 && p > 0 && p < nhas) {
+          for (int j = 0; j < n_sample; ++j) sample[j] = key[j * stride];
+          const int32_t bound = (vec ? sample_bound_avx2 : sample_bound_base)(sample.data(), n_sample, srank);
+          // (a block that has no state yet is below any bound but the lowest key)
+          if (bound != std::numeric_limits<int32_t>::min()) {
+            m = (vec ? collect_avx2 : collect_base)(key.data(), N, bound, ci.data());
+            if (m < p || m > N / 2) m = -1;
+          }
         }
         if (m < 0) {
           m = 0;
@@ -212,24 +247,11 @@ double objective(const float* scores, int B, int T, int N, const int32_t* born, 
             }
           }
           top_k(ck.data(), ci.data(), m, p, inP, tk);
-          bounded = 2 * (int64_t)p < m;
-          if (bounded) {
-            std::nth_element(ck.begin(), ck.begin() + 2 * p, ck.begin() + m, std::greater<uint32_t>());
-            bound = (int32_t)(ck[2 * p] ^ 0x80000000u);
-          }
         } else {
           order.clear();
           for (int j = 0; j < m; ++j) order.push_back(pack(ranked(key[ci[j]]), ci[j]));
           std::nth_element(order.begin(), order.begin() + (p - 1), order.end(), std::greater<uint64_t>());
           for (int j = 0; j < p; ++j) inP[~(uint32_t)order[j] & 0xffffffffu] = 1;
-          if (m > 3 * (int64_t)p) {  // (the bound only rises while there are candidates to spare)
-            std::nth_element(order.begin() + p, order.begin() + 2 * p, order.end(), std::greater<uint64_t>());
-            bound = (int32_t)((uint32_t)(order[2 * p] >> 32) ^ 0x80000000u);
-          } else if (m - p < p / 2) {  // (and is found anew before they run out)
-            bounded = false;
-          }
-          // a block that has no state yet is below any bound but the lowest key
-          if (bound == std::numeric_limits<int32_t>::min()) bounded = false;
         }
         const size_t r = (size_t)b * T + phi;
         double hit = 0.0;

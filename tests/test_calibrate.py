@@ -70,7 +70,7 @@ def test_calibrate_growing_blocks_and_threads():
 @pytest.mark.parametrize("k,p,drift,step", [(12, 0, 0.02, 0.0), (12, 9, 0.5, 0.25), (40, 160, 0.1, 1.0), (1, 1, 0.0, 0.0),
                                             (30, 299, 0.3, 0.0)])
 def test_calibrate_candidate_bound(k, p, drift, step):
-    """Rows ranked through the bound kept from the row before: slow and fast drifts, scores on a
+    """Rows ranked through the bound of a sample of their keys: slow and fast drifts, scores on a
     grid (hundreds of ties), budgets up to every block, blocks that form late over NaN entries;
     every objective is the oracle's."""
     L = _lib()
@@ -87,6 +87,48 @@ def test_calibrate_candidate_bound(k, p, drift, step):
     clean = np.nan_to_num(traj.astype(np.float64))
     ref = np.array([O.calibration_objective(clean, k, tuple(float(x) for x in th), p or None, fr) for th in grid])
     np.testing.assert_allclose(obj, ref, rtol=0, atol=1e-12)
+
+
+def _moving_trajectory(seed, rows, blocks, move):
+    """AR(1) scores whose rows shift by N(0, move) as a whole, as block scores do with the query's norm."""
+    rng = np.random.default_rng(seed)
+    x, out = rng.normal(size=blocks), np.empty((rows, blocks), dtype=np.float32)
+    for r in range(rows):
+        out[r] = 45.0 + move * rng.normal() + 1.6 * x
+        x = 0.95 * x + np.sqrt(1 - 0.95 ** 2) * rng.normal(size=blocks)
+    return out
+
+
+@pytest.mark.parametrize("blocks,k,p", [(1024, 16, 0), (1500, 100, 150), (1200, 3, 1), (3000, 700, 1400), (513, 200, 0)])
+def test_calibrate_moving_rows(blocks, k, p):
+    """Budgets on both sides of the sample's limits, rows of ties in stretches, late blocks."""
+    L = _lib()
+    traj = _moving_trajectory(blocks + k, 10, blocks, 3.0)
+    traj[3:6] = np.round(traj[3:6])
+    traj[7, : blocks // 2] = traj[7, 0]
+    fr = np.zeros(blocks, dtype=np.int32)
+    fr[-9:] = np.arange(9)
+    grid = np.asarray(O.THETA_GRID, dtype=np.float32)[::11]
+    _, obj = L.prr_calibrate(traj, k, grid, p_select=p, n_threads=3, form_row=fr)
+    ref = np.array([O.calibration_objective(traj.astype(np.float64), k, tuple(float(x) for x in th), p or None, fr)
+                    for th in grid])
+    np.testing.assert_allclose(obj, ref, rtol=0, atol=1e-12)
+
+
+def test_calibrate_time_of_moving_rows():
+    """Rows that move as a whole take no longer than rows that do not (three times as long where a
+    row's candidates depend on the row before)."""
+    import time
+    L = _lib()
+    grid = np.asarray(O.THETA_GRID, dtype=np.float32)
+    trajs = [_moving_trajectory(5, 24, 8192, move) for move in (0.0, 3.0)]
+    best = [np.inf, np.inf]
+    for _ in range(6):
+        for i, t in enumerate(trajs):
+            t0 = time.perf_counter()
+            L.prr_calibrate(t, 256, grid, n_threads=2)
+            best[i] = min(best[i], time.perf_counter() - t0)
+    assert best[1] < 1.7 * best[0], best
 
 
 def test_calibrate_formation_pins_natively():
