@@ -6,6 +6,8 @@
 // Included by one translation unit per 16-bit type (they compile in parallel).
 #pragma once
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "prr_device.h"
@@ -257,7 +259,7 @@ __device__ __forceinline__ AttnCtx attn_ctx(const A& a, int h) {
 
 constexpr int kOPad = kHeadDim + 4;  // LDS row stride of a head's partial output
 
-struct UnitLds {
+struct __align__(16) UnitLds {  // (rows are read and written 16 bytes at a time)
   float wo[4][16][kOPad];
   float wm[4][16];
   float wl[4][16];
@@ -501,6 +503,7 @@ struct SpecLds {
   UnitLds unit;
   int32_t ids[16];
 };
+static_assert(offsetof(SpecLds, unit) % 16 == 0, "16-byte rows in LDS");
 
 template <bool BF16, int PS>
 __global__ __launch_bounds__(256) void spec_attn_kernel(const SpecLaunch a) {
@@ -547,7 +550,7 @@ __global__ __launch_bounds__(256) void select_spec_kernel(const ScoreLaunch a, c
 constexpr float kMaxWastedShare = 0.875f;
 constexpr int kSpinLimit = 1 << 24;
 
-struct MergeLds {  // each wave's running state
+struct __align__(16) MergeLds {  // each wave's running state
   float acc[4][kHeadDim];
   float ml[4][2];
 };
@@ -564,13 +567,14 @@ struct RepairLds {
   int32_t wpages[16];
   int32_t xpages[16];
   int32_t xslots[16];
-  float fred[2][16];
   int nWp, nXp;
   union {
     UnitLds unit;    // work workgroups
     MergeLds merge;  // merge workgroups
   };
 };
+static_assert(offsetof(RepairLds, unit) % 16 == 0 && offsetof(RepairLds, merge) % 16 == 0 && kOPad % 4 == 0,
+              "16-byte rows in LDS");
 
 // Folds of a merge wave: the states i = w, w + 4, .. < n of one query head into the running
 // (M, L, ax, ay), where ml(i, m, l) gives state i's (m, l) and out(i) its outputs at columns
