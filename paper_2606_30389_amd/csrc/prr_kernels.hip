@@ -666,7 +666,9 @@ __global__ __launch_bounds__(1024) void score_topk_block_kernel(const ScoreLaunc
 
   const int n = a.num_pages;
   switch (select_j(n)) {
-    case 1:  // (not launched for so few pages)
+    case 1:  // (not launched for up to 512 pages; 513 to 1024 take a key per thread)
+      select_scores<1>(scores, n, a, h, ss);
+      break;
     case 2: select_scores<2>(scores, n, a, h, ss); break;
     case 4: select_scores<4>(scores, n, a, h, ss); break;
     case 8: select_scores<8>(scores, n, a, h, ss); break;

@@ -30,7 +30,7 @@ namespace {
 // over more of them (fewer pages yet would cost more in the arrival counter, about 12 ns a
 // workgroup, than the shorter scan gains).  Whole call, every head (8 KV heads x 16384 pages,
 // 256 selected): 40.9 us with 64 pages per 1024-thread workgroup and a select over all keys in
-// registers, 21.1 now; 8 x 4096: 14.0 -> 10.8; 2 x 8192: 11.9 -> 11.6.
+// registers, 21.1 now; 8 x 4096: 14.0 -> 10.8.
 constexpr int kScorePagesPerIt = 4 * kTopkWaves;
 
 template <int IT>
@@ -122,7 +122,7 @@ __device__ __forceinline__ void role_score_topk(const ScoreLaunch& a, int blk, i
   // scores and group keys are published with device-coherent stores, completed before the
   // counter is bumped, and read back the same way
   float* scores = a.scores + (size_t)h * a.max_pages;
-  uint32_t* gmax = a.gmax ? a.gmax + (size_t)h * a.gmax_stride : nullptr;
+  uint32_t* gmax = a.gmax + (size_t)h * a.gmax_stride;  // (used only with groups)
   if (w == 0) {
     constexpr int kPages = IT * kScorePagesPerIt;
 #pragma unroll
@@ -131,7 +131,7 @@ __device__ __forceinline__ void role_score_topk(const ScoreLaunch& a, int blk, i
       const bool ok = x < kPages && p < n;
       const float s = S.sc[min(x, kPages - 1)];
       if (ok) st_dev(&scores[p], s);
-      if (gmax && a.gshift) publish_groups(ok ? score_key(s) : 0u, ok ? p : n, n, a.gshift, gmax);
+      if (a.gshift) publish_groups(ok ? score_key(s) : 0u, ok ? p : n, n, a.gshift, gmax);
     }
     stores_complete();
     if (lane == 0) S.last = counter_add(&a.counters[h * a.cnt_stride], 1u) == (uint32_t)(a.nblk - 1);
@@ -140,15 +140,8 @@ __device__ __forceinline__ void role_score_topk(const ScoreLaunch& a, int blk, i
   if (!S.last) return;
 
   const auto key_of = [&](int p) { return score_key(ld_dev(&scores[p])); };
-  const auto gmax_of = [&](int g) {
-    if (gmax) return ld_dev(&gmax[g]);
-    // (no room for the groups' keys in the caller's scratch)
-    uint32_t m = 0u;
-    for (int i = 0; i < 1 << a.gshift; ++i) m = max(m, key_of(min((g << a.gshift) + i, n - 1)));
-    return m;
-  };
-  topk_select(n, a.gshift, a.kextra, a.forced, a.n_forced, gmax_of, key_of, a.selected + (size_t)h * a.cap, a.cap,
-              a.selected_count + h, S.top);
+  topk_select(n, a.gshift, a.kextra, a.forced, a.n_forced, [&](int g) { return ld_dev(&gmax[g]); }, key_of,
+              a.selected + (size_t)h * a.cap, a.cap, a.selected_count + h, S.top);
   if (t == 0) atomicExch(&a.counters[h * a.cnt_stride], 0u);
 }
 
@@ -1062,15 +1055,44 @@ void plan_predict(PredictLaunch& b) {
   b.gshift = topk_group_shift(b.num_pages);
 }
 
+bool no_groups(const ScoreLaunch& a) { return topk_group_shift(a.num_pages) > 0 && !a.gmax; }
+
+// Whether the scoring workgroups of this file and the select of prr_topk.h are quicker than the
+// block-wide ones (score_topk_block_kernel), whose scan of the metadata takes longer, by heads x
+// pages, and whose select of registers is quicker, above all for large budgets and up to 8192
+// pages.  Over 1 to 16 KV heads x 64 to 16384 pages x budgets of 16 to n / 8 (us, here / block):
+// 1 x 256 pages 7.2 / 7.6; 1 x 4096, 256 selected 11.1 / 9.1; 2 x 8192, 256: 12.4 / 11.5; 2 x
+// 16384, 512: 19.1 / 19.7; 4 x 8192, 256: 14.3 / 15.9; 8 x 2048, 128: 10.3 / 8.7; 8 x 4096, 512:
+// 14.8 / 14.3; 8 x 8192, 256: 16.1 / 21.1; 16 x 2500, 156: 13.1 / 15.0.  By this rule the worst of
+// them takes 6 % longer than the better of the two.  Without scratch for the groups' keys the
+// block-wide ones are (static entry, 8 x 2500, 156: 19.1 / 12.7).
+bool score_spread(const ScoreLaunch& a) {
+  const int n = a.num_pages;
+  if (n <= 2 * kTopkThreads) return true;
+  if (no_groups(a) || topk_crowded(n, a.kextra, a.n_forced)) return false;
+  return (int64_t)a.num_kv_heads * n + (n > 8192 ? 8000 : 0) >= 16400 + 40 * (int64_t)(a.kextra + a.n_forced);
+}
+
+// The same for the EMA update and prediction with scratch, against predict_kernel's one workgroup
+// per KV head (2 KV heads, us here / there: 256 pages, 32 predicted 4.2 / 4.9; 1024, 64: 5.5 / 4.9;
+// 4096, 256: 8.2 / 6.2; 8192, 256: 8.8 / 8.9; 8192, 1024: 13.3 / 9.7; 16384, 512: 12.2 / 14.9).
+bool predict_spread(const PredictLaunch& a) {
+  const int n = a.num_pages;
+  return n <= kTopkThreads || (n > 4096 && 20 * (a.kextra + a.n_forced) <= n);
+}
+
+// Beside the repair the update costs no launch of its own, which pays for more: 8 KV heads, us a
+// layer with it / with predict_kernel after the repair: 2048 pages, 512 predicted 38.0 / 42.5;
+// 6000, 1024: 62.5 / 67.0; 4096, 1024: 79.6 / 73.5; 2500, 625: 60.5 / 56.9.
+bool predict_alone(const PredictLaunch& a) {
+  return topk_group_shift(a.num_pages) > 0 && 5 * (a.kextra + a.n_forced) > a.num_pages;
+}
+
 }  // namespace
 
 template <bool BF16>
 hipError_t launch_score_topk_t(ScoreLaunch a, hipStream_t stream) {
-  // The block-wide select where the bound drops too few keys (2 KV heads, 1024 of 4096 pages:
-  // 8.7 us, 24.9 here) and where two keys per thread of 1024 beat eight per thread of 256
-  // (128 of 2048 pages: 8.8 us, 9.6 here; up to 1024 pages 8.8 and 8.5).
-  if (topk_crowded(a.num_pages, a.kextra, a.n_forced) || (a.num_pages > 1024 && a.num_pages <= kTopkDirect))
-    return launch_score_topk_block(a, stream);
+  if (!score_spread(a)) return launch_score_topk_block(a, stream);
   const int it = plan_score(a);
   const dim3 grid(a.nblk, a.num_kv_heads);
   return it == kScoreItMany ? launch((const void*)score_topk_kernel<BF16, kScoreItMany>, grid, stream, a)
@@ -1086,7 +1108,7 @@ hipError_t launch_spec_attn_t(const SpecLaunch& a, hipStream_t stream) {
 
 template <bool BF16>
 hipError_t launch_select_spec_t(ScoreLaunch a, const SpecLaunch& b, hipStream_t stream) {
-  if (topk_crowded(a.num_pages, a.kextra, a.n_forced)) {
+  if (no_groups(a) || topk_crowded(a.num_pages, a.kextra, a.n_forced)) {
     const hipError_t e = launch_score_topk_block(a, stream);
     return e != hipSuccess ? e : launch_spec_attn_t<BF16>(b, stream);
   }
@@ -1107,6 +1129,10 @@ hipError_t launch_repair_t(const RepairLaunch& a, hipStream_t stream) {
 
 template <bool BF16>
 hipError_t launch_repair_predict_t(const RepairLaunch& a, PredictLaunch b, hipStream_t stream) {
+  if (predict_alone(b)) {
+    const hipError_t e = launch_repair_t<BF16>(a, stream);
+    return e != hipSuccess ? e : launch_predict(b, stream);
+  }
   plan_predict(b);
   return by_page_size(a.page_size, [&](auto ps) {
     return launch((const void*)repair_predict_kernel<BF16, ps()>, dim3(a.num_kv_heads * (a.nwork + a.group + b.nblk)),

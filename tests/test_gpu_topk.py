@@ -184,3 +184,38 @@ def test_repair_calls_of_other_sizes_share_a_workspace():
     for o, l in results[True] + results[False]:
         assert (o - results[True][0][0]).abs().max() < 1e-4 and torch.allclose(l, results[True][0][1], rtol=1e-4)
     assert int(st.workspace[0]) == 0  # no error flag
+
+
+def _us(torch, fn, iters=30, reps=5):
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        fn()
+        a.record()
+        for _ in range(iters):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / iters)
+    return best
+
+
+@pytest.mark.parametrize("hkv,n,k", [(1, 4096, 1024), (2, 2500, 625), (2, 4096, 256), (8, 2500, 600), (1, 8192, 1024)])
+def test_selection_takes_the_quicker_kernels(hkv, n, k):
+    """Where few heads and pages or large budgets make the block-wide kernels the quicker ones, no
+    entry takes the others, which need 1.4 to 2.9 times as long there: step 0 against its two
+    calls, the selection without scratch against the one with it."""
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    from paper_2606_30389_amd import runtime as R
+    rng = np.random.default_rng(n + k)
+    vals = (45 + rng.standard_normal((hkv, n))).astype(np.float32)
+    pc, st, q = _score_layer(torch, vals, k, [])
+    stack = R.DecodeStack([st], [q], torch.device("cuda:0"))
+    stream = torch.cuda.current_stream()
+    step = _us(torch, lambda: stack.step(L.PRR_SCHED_PREFILL, stream))
+    select, predict = _us(torch, lambda: st.select(q)), _us(torch, lambda: st.predict())
+    counters = _us(torch, lambda: L.prr_score_topk(st.dims, q, st.meta, n, k, [], True, st.scores, st.sel, st.sel_count,
+                                                   st.cap, st.workspace, 512))
+    S.log(f"hkv={hkv} n={n} k={k}: step 0 {step:.1f} us, its calls {select:.1f} + {predict:.1f}, counters {counters:.1f}")
+    assert step <= 1.15 * (select + predict) and counters <= 1.25 * select
