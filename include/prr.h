@@ -346,7 +346,8 @@ typedef struct {
  * written on `stream`): the select / speculate / repair / predict steps of Fig. 1 and
  * Section 4, launched from native code.
  *   events      host [3 * n_layers + 1] hipEvent_t created by the caller (timing may be
- *               disabled) that order the two streams in PRR_SCHED_TWO_STREAM, else ignored; NULL
+ *               disabled), the first four of which order the two streams in
+ *               PRR_SCHED_TWO_STREAM, else ignored; NULL
  *               with PRR_SCHED_TWO_STREAM orders the two streams with stream memory writes
  *               and waits instead (hipStreamWriteValue64 / hipStreamWaitValue64 on four
  *               64-bit words that the library allocates once per device and keeps until the
@@ -359,7 +360,7 @@ typedef struct {
  * When the call returns every launch is enqueued; all work of the step is ordered
  * before any later work on `stream` and on `spec_stream`.  The
  * arguments of every layer are validated as by the individual calls; on an error in
- * layer l, layers before l have been enqueued. */
+ * layer l, layers before l have been enqueued (and are ordered before later work likewise). */
 prr_status prr_decode_step(const prr_dims* dims, const prr_step_params* params, const prr_layer_io* layers,
                            int32_t n_layers, int32_t parity, int32_t schedule, hipStream_t stream,
                            hipStream_t spec_stream, hipEvent_t* events);

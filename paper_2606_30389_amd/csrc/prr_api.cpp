@@ -930,8 +930,7 @@ static prr_status two_stream_step(const prr_dims* dims, const prr_step_params* s
   const auto event = [&](int i) { return mem ? nullptr : events[i]; };
   PRR_TRY(stream_dep(stream, spec_stream, event(0), mem, 2));
   PRR_TRY(stream_dep(spec_stream, stream, event(1), mem, 3));
-  for (int l = 0; l < n_layers; ++l) {
-    const prr_layer_io& y = layers[l];
+  const auto layer = [&](const prr_layer_io& y) {
     const float* th = y.theta ? y.theta : &sp->alpha;  // (alpha, beta, gamma are consecutive)
     PRR_TRY(check_theta(th));
     prr::ScoreLaunch sc;
@@ -952,16 +951,25 @@ static prr_status two_stream_step(const prr_dims* dims, const prr_step_params* s
                          y.predicted_count[1 - parity], sp->cap, pr));
     predict_scratch(y.workspace, L, pr);
     PRR_TRY(hip_status(prr::launch_select_spec(sc, at, stream), "select + speculate launch"));
-    PRR_TRY(hip_status(prr::launch_repair_predict(re, pr, stream), "repair + predict launch"));
-  }
-  // later work on the speculation stream comes after the step, as it would had the predictions
-  // been made there
-  PRR_TRY(stream_dep(stream, spec_stream, event(2), mem, 4));
-  // (a captured stream has to be joined back; outside a capture nothing is left to wait for)
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
-  if (capturing == hipStreamCaptureStatusActive) PRR_TRY(stream_dep(spec_stream, stream, event(3), mem, 5));
-  return ok();
+    return hip_status(prr::launch_repair_predict(re, pr, stream), "repair + predict launch");
+  };
+  prr_status st = PRR_OK;
+  for (int l = 0; l < n_layers && st == PRR_OK; ++l) st = layer(layers[l]);
+  // Later work on the speculation stream comes after the step, as it would had the predictions
+  // been made there; after an error, behind the layers that have been enqueued.
+  char why[sizeof(g_last_error)];
+  memcpy(why, g_last_error, sizeof(why));
+  const prr_status end = [&] {
+    PRR_TRY(stream_dep(stream, spec_stream, event(2), mem, 4));
+    // (a captured stream has to be joined back; outside a capture nothing is left to wait for)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) (void)hipGetLastError();
+    if (capturing == hipStreamCaptureStatusActive) PRR_TRY(stream_dep(spec_stream, stream, event(3), mem, 5));
+    return ok();
+  }();
+  if (st == PRR_OK) return end;
+  memcpy(g_last_error, why, sizeof(why));
+  return st;
 }
 
 prr_status prr_decode_step(const prr_dims* dims, const prr_step_params* sp, const prr_layer_io* layers,

@@ -186,6 +186,39 @@ def test_repair_calls_of_other_sizes_share_a_workspace():
     assert int(st.workspace[0]) == 0  # no error flag
 
 
+@pytest.mark.parametrize("events", [True, False])
+def test_two_stream_step_that_fails_orders_its_layers(events):
+    """A later layer's invalid arguments end the step with its own message; the layers before it
+    still run ahead of what the caller enqueues on the speculation stream next."""
+    import torch
+    from paper_2606_30389_amd import _lib as L
+    from paper_2606_30389_amd import runtime as R
+    n, reps = 3000, 100
+    vals = (45 + np.random.default_rng(5).standard_normal((2, n))).astype(np.float32)
+    pc, st, q = _score_layer(torch, vals, 64, [])
+    dev = torch.device("cuda:0")
+    stack = R.DecodeStack([st] * (reps + 1), [q] * (reps + 1), dev)  # the same layer again and again
+    s, spec = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    one = R.DecodeStack([st], [q], dev)
+    one.step(L.PRR_SCHED_PREFILL, s)
+    torch.cuda.synchronize()
+    st.level.zero_()  # (each pass moves it half way towards the scores)
+    st.trend.zero_()
+    torch.cuda.synchronize()
+    stack.io[reps].ws_bytes = 16
+    stack.params.epoch = 0
+    with pytest.raises(L.PrrError, match="workspace of 16 bytes too small"):
+        L.prr_decode_step(stack.dims, stack.params, stack.io, st.cur, L.PRR_SCHED_TWO_STREAM, s, spec,
+                          stack.events if events else None)
+    with torch.cuda.stream(spec):
+        level, trend, count = st.level.clone(), st.trend.clone(), st.pred_count[1 - st.cur].clone()
+    torch.cuda.synchronize()
+    assert torch.equal(level, st.level) and torch.equal(trend, st.trend)
+    assert torch.equal(count, st.pred_count[1 - st.cur]) and int(count[0]) == 64
+    assert float((level[:, :n].cpu() - torch.from_numpy(vals)).abs().max()) < 1e-3
+
+
 def _us(torch, fn, iters=30, reps=5):
     best = float("inf")
     for _ in range(reps):
