@@ -163,13 +163,13 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
   int valid[S::kPages];
   bool ok[S::kPages];
   meta_pages<PS>(k, ptab, num_tokens, page_end, max_pages, h, first, cg, src, valid, ok);
-  float mn[S::kPages][8], nx[S::kPages][8];  // smallest value, smallest negated value
+  float mn[S::kPages][8], mx[S::kPages][8];
 #pragma unroll
   for (int j = 0; j < S::kPages; ++j) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       mn[j][e] = __builtin_inff();
-      nx[j][e] = __builtin_inff();
+      mx[j][e] = -__builtin_inff();
     }
   }
 #pragma unroll
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
           for (int e = 0; e < 8; ++e) {
             const float f = u4_elem<BF16>(u, e);
             mn[j][e] = fminf(mn[j][e], f);
-            nx[j][e] = fminf(nx[j][e], -f);
+            mx[j][e] = fmaxf(mx[j][e], f);
           }
         }
       }
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void meta_minmax_kernel(const uint16_t* __rest
     float z[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float x = mn[j][e], y = nx[j][e];
+      float x = mn[j][e], y = -mx[j][e];
       swap_odd_rows(x, y);
       z[e] = fminf(x, y);
     }
