@@ -190,10 +190,10 @@ inline uint32_t ranked(int32_t key) { return (uint32_t)key ^ 0x80000000u; }  // 
 //
 // The time goes to passes over all blocks, so a row makes three plain ones (keys, collect,
 // EMA) and ranks few: keys taken at a stride give a bound that about 2p blocks reach, and those
-// are ordered exactly.  Rows where fewer than p or more than a quarter of the blocks reach it,
+// are ordered exactly.  Rows where fewer than p or more than half of the blocks reach it,
 // and budgets too large for that, rank every block by top_k.  The bound is each row's own: the
-// scores of a row move as a whole with the query, so a key kept from the row before (as it was
-// once) missed the range on half of the rows of real trajectories.  64 rows x 8192 blocks, 80
+// scores of a row move as a whole with the query, so that a key kept from the row before misses
+// the range on half of the rows of real trajectories.  64 rows x 8192 blocks, 80
 // grid points, 8 threads; one scalar pass that ranks every block, a bound from the row before,
 // this: rows of fixed mean 56-71, 22-27, 23-25 ms; Quest scores of 16 query heads (correlation 0.95 between rows)
 // 61-75, 65-70, 22; of 4 (0.85) 64-72, 82-90, 24.

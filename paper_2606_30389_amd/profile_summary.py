@@ -26,7 +26,7 @@ import sys
 
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-# the sources of the fused step kernel (the separate kernels live in prr_kernels.hip)
+# the sources of the fused step kernel (the separate kernels live in prr_sep.h and prr_kernels.hip)
 DEVICE_SOURCES = ("prr_fused_impl.h", "prr_fused_bf16.hip", "prr_fused_f16.hip", "prr_fused_p64.hip", "prr_select.h",
                   "prr_device.h", "prr_launch.h")
 
