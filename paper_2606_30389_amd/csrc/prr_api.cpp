@@ -119,8 +119,11 @@ bool ws_layout(const prr_dims* d, int cap, int chunk, WsLayout& L) {
   off = align_up(off + (size_t)hkv * L.nwork_max * g * 2 * 8, 256);
   L.rep_o = off;
   off = align_up(off + (size_t)hkv * L.nwork_max * g * 128 * 4, 256);
-  // fused step: tagged scores, threshold, missed count and list, partial states
+  // fused step: tagged scores, threshold, missed count and list, partial states; from a multiple
+  // of 64 KB on, so that the regions before it do not decide which memory channels its polled words
+  // share (40 layers of 2 KV heads x 8192 pages: 584-585 us a step, 588-589 at a multiple of 256)
   L.nparts = 3 * L.nchunks;
+  off = align_up(off, 65536);
   L.f_score = off;
   off = align_up(off + (size_t)hkv * d->max_pages * 8, 256);
   // the threshold, missed and late counts: 8 copies of 256 bytes per KV head
